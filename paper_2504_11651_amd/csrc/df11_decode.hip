@@ -63,54 +63,54 @@ __global__ __launch_bounds__(64 * W) void df11_decode_wave_kernel(DecodeArgs a) 
     // the first block's words are requested before the tables are staged,
     // so the two memory round trips overlap
     ChunkWords cw{};
-    if (first_block < a.num_blocks) cw = load_chunk(a, first_block, first_block * 64u + lane);
+    if (first_block < a.num_blocks) cw = load_chunk<64>(a, first_block, lane);
     stage_table_blob(a, lds, tid, 64 * W);
     const Tables tb = stage_tables(a, lds);
-    uint8_t *buf = lds + a.table_lds_bytes + wave * a.buf_bytes;
-    uint32_t *buf32 = reinterpret_cast<uint32_t *>(buf);
-    const uint32_t cap = a.buf_bytes - 8u;
+    const uint32_t buf_off = a.table_lds_bytes + wave * a.buf_bytes;
+    uint8_t *buf = lds + buf_off + kBufLead;
     __syncthreads();
     if (first_block >= a.num_blocks) return;
-    Chunk ch = chunk_setup(a, cw, first_block * 64u + lane);
+    Chunk ch[1] = {chunk_setup<64>(a, cw, first_block, lane)};
     Range r = block_range(a, cw);
 
     for (uint32_t b = first_block; b < a.num_blocks; b += stride) {
         // loads for this block's assembly and the next block's decode
         const uint32_t bn = b + stride;
         ChunkWords nxt = cw;
-        if (bn < a.num_blocks) nxt = load_chunk(a, bn, bn * 64u + lane);
+        if (bn < a.num_blocks) nxt = load_chunk<64>(a, bn, lane);
+        const Groups<kPre> gr = block_groups<kPre>(r, lane, 64u);
         uint2 S[kPre];
-        prefetch_sm(a, r, lane, 64u, S);
+        prefetch_sm(a, r, gr, S);
         const uint32_t edge_sm = prefetch_edge_sm(a, r, lane);
 
+        if (a.hold) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");  // as below, 5 issued
         wave_lds_sync();  // this wave's reads of the previous block are issued
         for (uint32_t i = lane; i < (a.buf_bytes >> 4); i += 64u)
-            reinterpret_cast<uint4 *>(buf)[i] = make_uint4(0u, 0u, 0u, 0u);
+            reinterpret_cast<uint4 *>(lds + buf_off)[i] = make_uint4(0u, 0u, 0u, 0u);
 
-        uint32_t sy[kKeep], npk[(kKeep + 3) / 4], p_rest;
-        const uint32_t cnt = decode_count(tb, ch, sy, npk, &p_rest);
-        const uint32_t excl = wave_inclusive_scan(cnt) - cnt;
+        Trail<kKeep> tr[1];
+        uint32_t state[1], out8[1];
+        decode_count(tb, ch, tr, state, out8);
+        const uint32_t excl8 = wave_inclusive_scan(out8[0]) - out8[0];
         // Waves near their memory phase issue first: the CU's decoding waves
         // (priority 0) fill the gaps, and the loads and stores of the waves
         // that have finished decoding reach the memory system sooner.
         __builtin_amdgcn_s_setprio(1);
         wave_lds_sync();
-        emit_exponents(tb, ch, sy, npk, p_rest, r.shift + excl, buf32, cap);
+        emit_exponents(tb, ch[0], tr[0], state[0], 8u * r.shift + excl8, buf_off, a.buf_bytes);
         wave_lds_sync();
 
         __builtin_amdgcn_s_setprio(2);
-        assemble_block(a, r, buf, lane, 64u, S, edge_sm);
+        assemble_block(a, r, buf, lane, 64u, gr, S, edge_sm);
         __builtin_amdgcn_s_setprio(0);
         cw = nxt;
-        ch = chunk_setup(a, cw, bn * 64u + lane);
+        ch[0] = chunk_setup<64>(a, cw, bn, lane);
         r = block_range(a, cw);
     }
 }
 
-// Lookups kept per chunk and sign/mantissa groups fetched at block start
-// when a lane owns two chunks (a 128-chunk block holds about twice the
-// outputs of a 64-chunk one).
-constexpr int kKeepPair = 10;
+// Sign/mantissa groups fetched at block start when a lane owns two chunks (a
+// 128-chunk block holds about twice the outputs of a 64-chunk one).
 constexpr int kPrePair = 7;
 
 // T = 128: one wave per block as well, lane l owning chunks 2l and 2l+1 of
@@ -127,46 +127,50 @@ __global__ __launch_bounds__(64 * W) void df11_decode_pair_kernel(DecodeArgs a) 
     const uint32_t first_block = xcd_grouped_index(blockIdx.x, gridDim.x) * W + wave;
     const uint32_t stride = gridDim.x * W;
     PairWords pw{};
-    if (first_block < a.num_blocks) pw = load_pair(a, first_block, first_block * 128u + 2u * lane);
+    if (first_block < a.num_blocks) pw = load_pair<128>(a, first_block, 2u * lane);
     stage_table_blob(a, lds, tid, 64 * W);
     const Tables tb = stage_tables(a, lds);
-    uint8_t *buf = lds + a.table_lds_bytes + wave * a.buf_bytes;
-    uint32_t *buf32 = reinterpret_cast<uint32_t *>(buf);
-    const uint32_t cap = a.buf_bytes - 8u;
+    const uint32_t buf_off = a.table_lds_bytes + wave * a.buf_bytes;
+    uint8_t *buf = lds + buf_off + kBufLead;
     __syncthreads();
     if (first_block >= a.num_blocks) return;
-    Chunk A, B;
-    pair_setup(a, pw, first_block * 128u + 2u * lane, A, B);
+    Chunk ch[2];
+    pair_setup<128>(a, pw, first_block, 2u * lane, ch);
     Range r = block_range(a, pw.bp0, pw.bp1);
 
     for (uint32_t b = first_block; b < a.num_blocks; b += stride) {
         const uint32_t bn = b + stride;
         PairWords nxt = pw;
-        if (bn < a.num_blocks) nxt = load_pair(a, bn, bn * 128u + 2u * lane);
+        if (bn < a.num_blocks) nxt = load_pair<128>(a, bn, 2u * lane);
+        const Groups<kPrePair> gr = block_groups<kPrePair>(r, lane, 64u);
         uint2 S[kPrePair];
-        prefetch_sm(a, r, lane, 64u, S);
+        prefetch_sm(a, r, gr, S);
         const uint32_t edge_sm = prefetch_edge_sm(a, r, lane);
+        // Vector memory operations complete in order: with the 8 just issued
+        // still out, the wave's stores before them are done.  It holds back
+        // nothing the block needs yet; it bounds what the wave has in flight.
+        if (a.hold) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
 
         wave_lds_sync();
         for (uint32_t i = lane; i < (a.buf_bytes >> 4); i += 64u)
-            reinterpret_cast<uint4 *>(buf)[i] = make_uint4(0u, 0u, 0u, 0u);
+            reinterpret_cast<uint4 *>(lds + buf_off)[i] = make_uint4(0u, 0u, 0u, 0u);
 
-        uint32_t syA[kKeepPair], npkA[(kKeepPair + 3) / 4], syB[kKeepPair],
-            npkB[(kKeepPair + 3) / 4], restA, restB, cntA, cntB;
-        decode_count_pair(tb, A, B, syA, npkA, syB, npkB, &restA, &restB, &cntA, &cntB);
-        const uint32_t cnt = cntA + cntB;
-        const uint32_t excl = wave_inclusive_scan(cnt) - cnt;
+        Trail<kKeep> tr[2];
+        uint32_t state[2], out8[2];
+        decode_count(tb, ch, tr, state, out8);
+        const uint32_t both8 = out8[0] + out8[1];
+        const uint32_t off8 = 8u * r.shift + wave_inclusive_scan(both8) - both8;
         __builtin_amdgcn_s_setprio(1);
         wave_lds_sync();
-        emit_exponents(tb, A, syA, npkA, restA, r.shift + excl, buf32, cap);
-        emit_exponents(tb, B, syB, npkB, restB, r.shift + excl + cntA, buf32, cap);
+        emit_exponents(tb, ch[0], tr[0], state[0], off8, buf_off, a.buf_bytes);
+        emit_exponents(tb, ch[1], tr[1], state[1], off8 + out8[0], buf_off, a.buf_bytes);
         wave_lds_sync();
 
         __builtin_amdgcn_s_setprio(2);
-        assemble_block(a, r, buf, lane, 64u, S, edge_sm);
+        assemble_block(a, r, buf, lane, 64u, gr, S, edge_sm);
         __builtin_amdgcn_s_setprio(0);
         pw = nxt;
-        pair_setup(a, pw, bn * 128u + 2u * lane, A, B);
+        pair_setup<128>(a, pw, bn, 2u * lane, ch);
         r = block_range(a, pw.bp0, pw.bp1);
     }
 }
@@ -186,53 +190,53 @@ __global__ __launch_bounds__(T / 2) void df11_decode_block_pair_kernel(DecodeArg
     const uint32_t lane = tid & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     PairWords pw{};
-    if (blockIdx.x < a.num_blocks) pw = load_pair(a, blockIdx.x, blockIdx.x * T + 2u * tid);
+    if (blockIdx.x < a.num_blocks) pw = load_pair<T>(a, blockIdx.x, 2u * tid);
     stage_table_blob(a, lds, tid, NT);
     const Tables tb = stage_tables(a, lds);
     uint32_t *wave_sums = reinterpret_cast<uint32_t *>(lds + a.table_lds_bytes);
-    uint8_t *const buf0 = lds + a.table_lds_bytes + 4 * kScanSlots;
-    const uint32_t cap = a.buf_bytes - 8u;
+    const uint32_t buf0 = a.table_lds_bytes + 4 * kScanSlots;
     __syncthreads();
     if (blockIdx.x >= a.num_blocks) return;
-    Chunk A, B;
-    pair_setup(a, pw, blockIdx.x * T + 2u * tid, A, B);
+    Chunk ch[2];
+    pair_setup<T>(a, pw, blockIdx.x, 2u * tid, ch);
     Range r = block_range(a, pw.bp0, pw.bp1);
 
     uint32_t parity = 0;
     for (uint32_t b = blockIdx.x; b < a.num_blocks; b += gridDim.x) {
         const uint32_t bn = b + gridDim.x;
         PairWords nxt = pw;
-        if (bn < a.num_blocks) nxt = load_pair(a, bn, bn * T + 2u * tid);
+        if (bn < a.num_blocks) nxt = load_pair<T>(a, bn, 2u * tid);
+        const Groups<kPrePair> gr = block_groups<kPrePair>(r, tid, NT);
         uint2 S[kPrePair];
-        prefetch_sm(a, r, tid, NT, S);
+        prefetch_sm(a, r, gr, S);
         const uint32_t edge_sm = prefetch_edge_sm(a, r, tid);
 
         // with two buffers this one was last read two blocks ago, before the
         // previous block's barriers
         if (!a.twin_bufs) __syncthreads();  // the previous block is assembled
-        uint8_t *buf = buf0 + (a.twin_bufs ? parity : 0u) * a.buf_bytes;
-        uint32_t *buf32 = reinterpret_cast<uint32_t *>(buf);
+        const uint32_t buf_off = buf0 + (a.twin_bufs ? parity : 0u) * a.buf_bytes;
+        uint8_t *buf = lds + buf_off + kBufLead;
         for (uint32_t i = tid; i < (a.buf_bytes >> 4); i += NT)
-            reinterpret_cast<uint4 *>(buf)[i] = make_uint4(0u, 0u, 0u, 0u);
+            reinterpret_cast<uint4 *>(lds + buf_off)[i] = make_uint4(0u, 0u, 0u, 0u);
 
-        uint32_t syA[kKeepPair], npkA[(kKeepPair + 3) / 4], syB[kKeepPair],
-            npkB[(kKeepPair + 3) / 4], restA, restB, cntA, cntB;
-        decode_count_pair(tb, A, B, syA, npkA, syB, npkB, &restA, &restB, &cntA, &cntB);
-        const uint32_t cnt = cntA + cntB;
-        const uint32_t incl = wave_inclusive_scan(cnt);
+        Trail<kKeep> tr[2];
+        uint32_t state[2], out8[2];
+        decode_count(tb, ch, tr, state, out8);
+        const uint32_t both8 = out8[0] + out8[1];
+        const uint32_t incl = wave_inclusive_scan(both8);
         if (lane == 63u) wave_sums[wave] = incl;
         __syncthreads();  // every wave's count is in, the buffer is cleared
         uint32_t before = 0;
         for (uint32_t w = 0; w < wave; ++w) before += wave_sums[w];
-        const uint32_t off = r.shift + before + incl - cnt;
-        emit_exponents(tb, A, syA, npkA, restA, off, buf32, cap);
-        emit_exponents(tb, B, syB, npkB, restB, off + cntA, buf32, cap);
+        const uint32_t off8 = 8u * r.shift + before + incl - both8;
+        emit_exponents(tb, ch[0], tr[0], state[0], off8, buf_off, a.buf_bytes);
+        emit_exponents(tb, ch[1], tr[1], state[1], off8 + out8[0], buf_off, a.buf_bytes);
         __syncthreads();  // the block's exponents are all in the buffer
 
-        assemble_block(a, r, buf, tid, NT, S, edge_sm);
+        assemble_block(a, r, buf, tid, NT, gr, S, edge_sm);
         parity ^= 1u;
         pw = nxt;
-        pair_setup(a, pw, bn * T + 2u * tid, A, B);
+        pair_setup<T>(a, pw, bn, 2u * tid, ch);
         r = block_range(a, pw.bp0, pw.bp1);
     }
 }
@@ -249,41 +253,43 @@ __global__ __launch_bounds__(T) void df11_decode_block_kernel(DecodeArgs a) {
     stage_table_blob(a, lds, tid, T);
     const Tables tb = stage_tables(a, lds);
     uint32_t *wave_sums = reinterpret_cast<uint32_t *>(lds + a.table_lds_bytes);
-    uint8_t *buf = lds + a.table_lds_bytes + 4 * kScanSlots;
-    uint32_t *buf32 = reinterpret_cast<uint32_t *>(buf);
-    const uint32_t cap = a.buf_bytes - 8u;
+    const uint32_t buf_off = a.table_lds_bytes + 4 * kScanSlots;
+    uint8_t *buf = lds + buf_off + kBufLead;
 
     if (blockIdx.x >= a.num_blocks) return;
-    ChunkWords cw = load_chunk(a, blockIdx.x, blockIdx.x * T + tid);
-    Chunk ch = chunk_setup(a, cw, blockIdx.x * T + tid);
+    ChunkWords cw = load_chunk<T>(a, blockIdx.x, tid);
+    Chunk ch[1] = {chunk_setup<T>(a, cw, blockIdx.x, tid)};
     Range r = block_range(a, cw);
 
     for (uint32_t b = blockIdx.x; b < a.num_blocks; b += gridDim.x) {
         const uint32_t bn = b + gridDim.x;
         ChunkWords nxt = cw;
-        if (bn < a.num_blocks) nxt = load_chunk(a, bn, bn * T + tid);
+        if (bn < a.num_blocks) nxt = load_chunk<T>(a, bn, tid);
+        const Groups<kPre> gr = block_groups<kPre>(r, tid, T);
         uint2 S[kPre];
-        prefetch_sm(a, r, tid, T, S);
+        prefetch_sm(a, r, gr, S);
         const uint32_t edge_sm = prefetch_edge_sm(a, r, tid);
 
         __syncthreads();  // tables staged / previous block's buffer consumed
         for (uint32_t i = tid; i < (a.buf_bytes >> 4); i += T)
-            reinterpret_cast<uint4 *>(buf)[i] = make_uint4(0u, 0u, 0u, 0u);
+            reinterpret_cast<uint4 *>(lds + buf_off)[i] = make_uint4(0u, 0u, 0u, 0u);
 
-        uint32_t sy[kKeep], npk[(kKeep + 3) / 4], p_rest;
-        const uint32_t cnt = decode_count(tb, ch, sy, npk, &p_rest);
+        Trail<kKeep> tr[1];
+        uint32_t state[1], out8[1];
+        decode_count(tb, ch, tr, state, out8);
 
-        const uint32_t incl = wave_inclusive_scan(cnt);
+        const uint32_t incl = wave_inclusive_scan(out8[0]);
         if (lane == 63u) wave_sums[wave] = incl;
         __syncthreads();
         uint32_t before = 0;
         for (uint32_t w = 0; w < wave; ++w) before += wave_sums[w];
-        emit_exponents(tb, ch, sy, npk, p_rest, r.shift + before + incl - cnt, buf32, cap);
+        emit_exponents(tb, ch[0], tr[0], state[0], 8u * r.shift + before + incl - out8[0], buf_off,
+                       a.buf_bytes);
         __syncthreads();
 
-        assemble_block(a, r, buf, tid, T, S, edge_sm);
+        assemble_block(a, r, buf, tid, T, gr, S, edge_sm);
         cw = nxt;
-        ch = chunk_setup(a, cw, bn * T + tid);
+        ch[0] = chunk_setup<T>(a, cw, bn, tid);
         r = block_range(a, cw);
     }
 }
@@ -307,11 +313,60 @@ std::mutex g_mu;
 std::vector<DeviceInfo> g_dev;
 
 constexpr uint32_t kWaveChoices[4] = {4, 8, 12, 16};
-// Waves per SIMD for a long stream: 5 beats 4 and 6 (a sixth adds contention
-// for memory and LDS, not throughput).  A short stream takes every wave that
-// fits when that removes a round of blocks per wave (its tail dominates).
-constexpr uint64_t kLongWavesPerSimd = 5;
-constexpr uint64_t kShortRounds = 4;
+
+// Waves per SIMD.  A stream's reads and writes are spread over every wave's
+// block, and the more blocks are in flight at once the less of the memory's
+// rate their mix reaches; fewer waves than the registers and LDS allow are
+// faster as soon as they still cover the decode's latency.  Times in us on
+// an MI355X, streams rotating so that none is cached; "before" is the same
+// rule's line when every wave decoded longer and 4 to 6 per SIMD were best.
+//   weights, T, mean code  before   2 waves   3 waves  3, hold   4 waves  4, hold   5 waves
+//   855.6 M  128  2.64      560       519       571      547       590
+//   218.1 M  128  2.64      140.1     130.2     142.1    134.3     149.2
+//   218.1 M  128  2.85      140.7     138.6     142.5    135.1     150.7
+//    80.0 M  128  2.64       52.7      51.2      53.8     51.5      54.4
+//    67.0 M  128  2.64       44.9      46.9      46.2               44.6
+//    16.0 M  128  2.64       14.6      15.7      13.4               13.2
+//   190.0 M   64  2.64      121.5     150         118.5             126.9    118.3     134.3
+//   100.0 M   64  2.85       66.2                  62.3             68.6     63.9      71.7
+//    50.0 M   64  2.85       30.6                  31.3             32.5     29.4      32.7
+//    50.0 M   64  2.64       31.0                  29.2             31.7               32.9
+//    24.0 M   64  2.64       16.8                  16.9             17.2     16.8      17.5
+//    20.0 M   64  2.85       15.7                  16.1             14.9               15.2
+//    16.8 M   64  2.64       13.1      17.0        13.7             13.0     13.2      12.7
+//   120.0 M  256  2.64       83.5     102          77.8             83.1               84.4
+//   120.0 M  256  2.85       84.7     114          84.8             83.1               87.2
+//   120.0 M  512  2.64       86.3     108                           78.6               78.7
+// "hold": a wave waits for its stores before it starts the next block.  It
+// takes the place of a third wave fewer where codes are longer: the lookups
+// per weight grow, and two waves no longer cover them.
+// A stream of few blocks per wave takes more waves instead: its last round
+// and the latency of each round dominate.
+struct WaveRule {
+    uint32_t per_simd;  // 0: every wave that fits
+    bool hold;
+};
+
+// Chunks per CU up to which a T = 64 stream takes 5 waves (2.65 rounds of
+// blocks), then 4 with hold (until 4.6 rounds of them, with long codes until
+// a stream is long), and from which a stream is long (12 rounds of two waves
+// on 128 chunks).
+constexpr uint64_t kFiveWaves = 3400, kFourWaves = 4725, kLongChunks = 12288;
+
+WaveRule wave_rule(const df11_stream *s, uint64_t cus) {
+    const df11_sizes &z = s->sizes;
+    const uint32_t T = s->layout.threads_per_block;
+    const bool long_codes = z.total_bits > z.n_elems * 11 / 4;  // mean above 2.75 bits
+    if (T == 64) {
+        if (z.num_chunks <= kFiveWaves * cus) return {5u, false};
+        if (z.num_chunks <= (long_codes ? kLongChunks : kFourWaves) * cus) return {4u, true};
+        return {3u, false};
+    }
+    if (z.num_chunks < kLongChunks * cus) return {0u, false};
+    if (T == 128) return {long_codes ? 3u : 2u, long_codes};
+    return {4u, false};
+}
+
 constexpr size_t kMaxShapes = 64;  // cached launch shapes per device
 
 KernelFn wave_kernel(uint32_t W) {
@@ -363,7 +418,7 @@ int fit(DeviceInfo &di, int slot, KernelFn fn, uint32_t threads, uint32_t lds, i
 }
 
 int shape_for(const df11_stream *s, KernelFn *fn, uint32_t *grid, uint32_t *block, uint32_t *lds,
-              uint32_t *twin_bufs) {
+              uint32_t *twin_bufs, uint32_t *hold) {
     const uint32_t T = s->layout.threads_per_block;
     const uint32_t K = s->layout.lut_bits;
     const uint32_t tab = static_cast<uint32_t>(df11tab::lds_bytes(K));
@@ -442,13 +497,10 @@ int shape_for(const df11_stream *s, KernelFn *fn, uint32_t *grid, uint32_t *bloc
     const uint64_t nb = s->sizes.num_blocks;
     const uint64_t blocks_needed = (nb + W - 1) / W;
     uint64_t per_cu = found->per_cu;
-    const uint64_t cap = kLongWavesPerSimd * 4 / W;  // 4 SIMDs per CU
-    if (T <= 128 && cap >= 1 && per_cu > cap) {
-        const uint64_t cus = static_cast<uint64_t>(di.cus);
-        const uint64_t rounds_all = (nb + cus * per_cu * W - 1) / (cus * per_cu * W);
-        const uint64_t rounds_cap = (nb + cus * cap * W - 1) / (cus * cap * W);
-        if (!(rounds_all < rounds_cap && rounds_all <= kShortRounds)) per_cu = cap;
-    }
+    const WaveRule rule = wave_rule(s, static_cast<uint64_t>(di.cus));
+    const uint64_t cap = rule.per_simd * 4ull * 64 / found->block;  // workgroups; 4 SIMDs per CU
+    if (cap >= 1 && per_cu > cap) per_cu = cap;
+    *hold = rule.hold;
     uint64_t g = static_cast<uint64_t>(di.cus) * per_cu;
     if (g > blocks_needed) g = blocks_needed;
     *grid = static_cast<uint32_t>(g ? g : 1);
@@ -465,8 +517,8 @@ int df11_decode_launch_shape(const df11_stream *s, uint32_t *grid, uint32_t *blo
     if (rc) return rc;
     if (!grid || !block || !lds_bytes) return DF11_E_INVALID_ARG;
     KernelFn fn;
-    uint32_t twin;
-    return shape_for(s, &fn, grid, block, lds_bytes, &twin);
+    uint32_t twin, hold;
+    return shape_for(s, &fn, grid, block, lds_bytes, &twin, &hold);
 }
 
 int df11_decode_block(const df11_stream *s, uint16_t *out, hipStream_t stream) {
@@ -475,8 +527,8 @@ int df11_decode_block(const df11_stream *s, uint16_t *out, hipStream_t stream) {
     if (s->sizes.n_elems == 0) return DF11_OK;
     if (!out || (reinterpret_cast<uintptr_t>(out) & 15u)) return DF11_E_INVALID_ARG;
     KernelFn fn;
-    uint32_t grid, block, lds, twin;
-    rc = shape_for(s, &fn, &grid, &block, &lds, &twin);
+    uint32_t grid, block, lds, twin, hold;
+    rc = shape_for(s, &fn, &grid, &block, &lds, &twin, &hold);
     if (rc) return rc;
     DecodeArgs a;
     a.exp = s->exp;
@@ -494,6 +546,7 @@ int df11_decode_block(const df11_stream *s, uint16_t *out, hipStream_t stream) {
     a.table_lds_bytes = static_cast<uint32_t>(df11tab::lds_bytes(s->layout.lut_bits));
     a.buf_bytes = buf_bytes_for(s->sizes.max_elems_per_block);
     a.twin_bufs = twin;
+    a.hold = hold;
     hipLaunchKernelGGL(fn, dim3(grid), dim3(block), lds, stream, a);
     return hipGetLastError() == hipSuccess ? DF11_OK : DF11_E_HIP;
 }

@@ -167,7 +167,7 @@ __device__ __forceinline__ void dot_block(const GemvArgs &g, const Range &r, con
             if ((E < lo && lo - E >= 8u) || E >= hi) return;  // (no E + 8: it may wrap)
             const uint32_t row = one_row ? rlo : rlo + (E >= b1 ? 1u : 0u) + (E >= b2 ? 1u : 0u);
             const uint32_t kcol = E - off - row * cols;
-            uint4 w = assemble_group(buf, gi, Sg);
+            uint4 w = assemble_group(reinterpret_cast<const uint2 *>(buf)[gi], Sg);
             uint4 xv = *reinterpret_cast<const uint4 *>(x + kcol);
             if (E < lo || hi - E < 8u) {  // a group shared with a neighbour: its elements only
                 const uint4 mk = element_mask(lo > E ? lo - E : 0u, umin(hi - E, 8u));
@@ -220,42 +220,42 @@ __global__ __launch_bounds__(64 * W) void df11_gemv_wave_kernel(GemvArgs g) {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // block indices stay scalar
     stage_table_blob(a, lds, tid, 64 * W);
     const Tables tb = stage_tables(a, lds);
-    uint8_t *buf = lds + a.table_lds_bytes + wave * a.buf_bytes;
-    uint32_t *buf32 = reinterpret_cast<uint32_t *>(buf);
-    const uint32_t cap = a.buf_bytes - 8u;
+    const uint32_t buf_off = a.table_lds_bytes + wave * a.buf_bytes;
+    uint8_t *buf = lds + buf_off + kBufLead;
     __syncthreads();
 
     const uint32_t first_block = xcd_grouped_index(blockIdx.x, gridDim.x) * W + wave;
     const uint32_t stride = gridDim.x * W;
     if (first_block >= a.num_blocks) return;
-    ChunkWords cw = load_chunk(a, first_block, first_block * 64u + lane);
-    Chunk ch = chunk_setup(a, cw, first_block * 64u + lane);
+    ChunkWords cw = load_chunk<64>(a, first_block, lane);
+    Chunk ch[1] = {chunk_setup<64>(a, cw, first_block, lane)};
     Range r = block_range(a, cw);
 
     for (uint32_t b = first_block; b < a.num_blocks; b += stride) {
         const uint32_t bn = b + stride;
         ChunkWords nxt = cw;
-        if (bn < a.num_blocks) nxt = load_chunk(a, bn, bn * 64u + lane);
+        if (bn < a.num_blocks) nxt = load_chunk<64>(a, bn, lane);
         uint2 S[kPre];
-        prefetch_sm(a, r, lane, 64u, S);
+        prefetch_sm(a, r, block_groups<kPre>(r, lane, 64u), S);
 
         wave_lds_sync();
         for (uint32_t i = lane; i < (a.buf_bytes >> 4); i += 64u)
-            reinterpret_cast<uint4 *>(buf)[i] = make_uint4(0u, 0u, 0u, 0u);
+            reinterpret_cast<uint4 *>(lds + buf_off)[i] = make_uint4(0u, 0u, 0u, 0u);
 
-        uint32_t sy[kKeep], npk[(kKeep + 3) / 4], p_rest;
-        const uint32_t cnt = decode_count(tb, ch, sy, npk, &p_rest);
-        const uint32_t excl = wave_inclusive_scan(cnt) - cnt;
+        Trail<kKeep> tr[1];
+        uint32_t state[1], out8[1];
+        decode_count(tb, ch, tr, state, out8);
+        const uint32_t excl8 = wave_inclusive_scan(out8[0]) - out8[0];
         __builtin_amdgcn_s_setprio(1);
         wave_lds_sync();
-        emit_exponents(tb, ch, sy, npk, p_rest, r.shift + excl, buf32, cap);
+        emit_exponents(tb, ch[0], tr[0], state[0], 8u * r.shift + excl8, buf_off, a.buf_bytes);
         wave_lds_sync();
 
         __builtin_amdgcn_s_setprio(2);
         dot_block(g, r, buf, lane, S, b);
         __builtin_amdgcn_s_setprio(0);
         cw = nxt;
-        ch = chunk_setup(a, cw, bn * 64u + lane);
+        ch[0] = chunk_setup<64>(a, cw, bn, lane);
         r = block_range(a, cw);
     }
 }
@@ -423,7 +423,7 @@ int df11_block_gemv(const df11_stream *dev, const df11_matrix *mats, uint32_t n_
     a.max_len = dev->sizes.max_code_len;
     a.table_lds_bytes = static_cast<uint32_t>(df11tab::lds_bytes(dev->layout.lut_bits));
     a.buf_bytes = buf_bytes_for(dev->sizes.max_elems_per_block);
-    a.twin_bufs = 0;  // not used by the fused kernel
+    a.twin_bufs = a.hold = 0;  // not used by the fused kernel
     g.n_mats = n_mats;
     g.part = static_cast<float *>(workspace);
     ReduceArgs ra{};
