@@ -321,25 +321,28 @@ constexpr uint32_t kWaveChoices[4] = {4, 8, 12, 16};
 // an MI355X, streams rotating so that none is cached; "before" is the same
 // rule's line when every wave decoded longer and 4 to 6 per SIMD were best.
 //   weights, T, mean code  before   2 waves   3 waves  3, hold   4 waves  4, hold   5 waves
-//   855.6 M  128  2.64      560       519       571      547       590
-//   218.1 M  128  2.64      140.1     130.2     142.1    134.3     149.2
+//   855.6 M  128  2.69      562       519       565      542       595
+//   300.0 M  128  2.59      192.2     176.0     194.1    185.5     204.7
+//   218.1 M  128  2.59      140.1     130.2     142.1    134.3     149.2
+//   218.1 M  128  2.64      140.3     135.4     142.3    134.6     149.8
+//    91.7 M  128  2.64       59.3      60.6      58.7     57.4      61.6
 //   218.1 M  128  2.85      140.7     138.6     142.5    135.1     150.7
-//    80.0 M  128  2.64       52.7      51.2      53.8     51.5      54.4
-//    67.0 M  128  2.64       44.9      46.9      46.2               44.6
-//    16.0 M  128  2.64       14.6      15.7      13.4               13.2
-//   190.0 M   64  2.64      121.5     150         118.5             126.9    118.3     134.3
+//    80.0 M  128  2.59       52.7      51.2      53.8     51.5      54.4
+//    67.0 M  128  2.59       44.9      46.9      46.2               44.6
+//    16.0 M  128  2.59       14.6      15.7      13.4               13.2
+//   190.0 M   64  2.59      121.5     150         118.5             126.9    118.3     134.3
 //   100.0 M   64  2.85       66.2                  62.3             68.6     63.9      71.7
 //    50.0 M   64  2.85       30.6                  31.3             32.5     29.4      32.7
-//    50.0 M   64  2.64       31.0                  29.2             31.7               32.9
-//    24.0 M   64  2.64       16.8                  16.9             17.2     16.8      17.5
+//    50.0 M   64  2.59       31.0                  29.2             31.7               32.9
+//    24.0 M   64  2.59       16.8                  16.9             17.2     16.8      17.5
 //    20.0 M   64  2.85       15.7                  16.1             14.9               15.2
-//    16.8 M   64  2.64       13.1      17.0        13.7             13.0     13.2      12.7
-//   120.0 M  256  2.64       83.5     102          77.8             83.1               84.4
+//    16.8 M   64  2.59       13.1      17.0        13.7             13.0     13.2      12.7
+//   120.0 M  256  2.59       83.5     102          77.8             83.1               84.4
 //   120.0 M  256  2.85       84.7     114          84.8             83.1               87.2
-//   120.0 M  512  2.64       86.3     108                           78.6               78.7
-// "hold": a wave waits for its stores before it starts the next block.  It
-// takes the place of a third wave fewer where codes are longer: the lookups
-// per weight grow, and two waves no longer cover them.
+//   120.0 M  512  2.59       86.3     108                           78.6               78.7
+// "hold": a wave waits for its stores before it starts the next block.  With
+// longer codes the lookups per weight grow and two waves no longer cover them;
+// a third one that holds does, without as many blocks in flight.
 // A stream of few blocks per wave takes more waves instead: its last round
 // and the latency of each round dominate.
 struct WaveRule {
@@ -350,8 +353,9 @@ struct WaveRule {
 // Chunks per CU up to which a T = 64 stream takes 5 waves (2.65 rounds of
 // blocks), then 4 with hold (until 4.6 rounds of them, with long codes until
 // a stream is long), and from which a stream is long (12 rounds of two waves
-// on 128 chunks).
-constexpr uint64_t kFiveWaves = 3400, kFourWaves = 4725, kLongChunks = 12288;
+// on 128 chunks) or very long.
+constexpr uint64_t kFiveWaves = 3400, kFourWaves = 4725, kLongChunks = 12288,
+                   kVeryLongChunks = 65536;
 
 WaveRule wave_rule(const df11_stream *s, uint64_t cus) {
     const df11_sizes &z = s->sizes;
@@ -363,7 +367,11 @@ WaveRule wave_rule(const df11_stream *s, uint64_t cus) {
         return {3u, false};
     }
     if (z.num_chunks < kLongChunks * cus) return {0u, false};
-    if (T == 128) return {long_codes ? 3u : 2u, long_codes};
+    if (T == 128) {
+        const bool mixed = z.total_bits * 50 > z.n_elems * 131;  // mean above 2.62 bits
+        const bool three = long_codes || (mixed && z.num_chunks < kVeryLongChunks * cus);
+        return {three ? 3u : 2u, three};
+    }
     return {4u, false};
 }
 

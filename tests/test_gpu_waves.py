@@ -22,11 +22,19 @@ def gaussian(n):
     return synth.gaussian(n, 0.02, 6)
 
 
+def two_sigmas(n):
+    """One code book for two standard deviations: a mean code of 2.67 bits."""
+    w = synth.gaussian(n, 0.02, 6)
+    w[:n // 2] = synth.gaussian(n // 2, 0.011, 7)
+    return w
+
+
 @pytest.mark.parametrize("T,make,n,per_simd", [
     (64, gaussian, 20_000_003, 5), (64, gaussian, 26_000_001, 4), (64, gaussian, 32_000_005, 3),
     (64, random_bits, 6_900_007, 5), (64, random_bits, 8_000_001, 4),
     (64, random_bits, 25_800_009, 3), (128, gaussian, 80_000_001, 2),
-    (128, random_bits, 25_800_009, 3), (256, gaussian, 80_000_001, 4)],
+    (128, two_sigmas, 80_000_001, 3), (128, random_bits, 25_800_009, 3),
+    (256, gaussian, 80_000_001, 4)],
     ids=lambda v: getattr(v, "__name__", str(v)))
 def test_waves_per_simd(T, make, n, per_simd):
     import torch
