@@ -9,17 +9,17 @@
 // (phase 1, prefix sum, phase 2 into LDS); then, in place of the stores, each
 // lane takes its 8-weight groups, assembles the BF16 values, and accumulates
 // their dot product with the matching 8 activations (v_dot2c_f32_bf16, fp32
-// accumulation).  A block covers at most two matrices and at most three rows
-// of each (columns >= 2048), so every lane keeps three partial sums per
-// matrix segment; a wave-wide sum turns them into at most 8 partial sums per
-// block, written to a workspace.  A second kernel adds, for every output row,
-// the partial sums of the blocks that cover it, in block order.  The result
-// depends only on the stream and the inputs (fixed summation order).
+// accumulation).  A block inside one matrix touches at most three of its rows
+// (columns >= 2048), so every lane keeps three partial sums; a block at a
+// boundary covers at most two matrices.  Wave-wide sums give at most 8
+// partial sums per block, written to a workspace.  A second kernel adds, for
+// every output row, the partial sums of the blocks that cover it, in a fixed
+// order.  The result depends only on the stream and the inputs.
 #include <hip/hip_runtime.h>
 
+#include <array>
 #include <cstdint>
 #include <mutex>
-#include <type_traits>
 #include <vector>
 
 #include "df11.h"
@@ -35,6 +35,8 @@ constexpr uint32_t kSegSlots = 4;              // partial sums per matrix segmen
 constexpr uint32_t kSlots = 2 * kSegSlots;     // per block
 constexpr uint32_t kMinCols = 2048;            // a block (<= 4096 weights) spans <= 3 rows
 constexpr uint32_t kMaxBlockElems = 64u * 64u; // 64 chunks of at most 64 codes
+
+constexpr uint32_t kNotStaged = 0xFFFFFFFFu;
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
@@ -73,6 +75,10 @@ struct GemvArgs {
     Divider div[kMaxM];   // division by cols
     const uint16_t *x[kMaxM];
     uint32_t row_base[kMaxM];  // index of the matrix's first row among all rows
+    uint32_t x_set[kMaxM];     // activations staged in LDS together: 1, 2, ... in matrix order
+    uint32_t x_at[kMaxM];      // where in LDS (kNotStaged: not there)
+    uint32_t x_bytes;          // LDS for activations
+    uint32_t boundary_grid;    // workgroups for the blocks at matrix boundaries
     float *part;               // kSlots floats per block
     uint32_t *first_block;     // per row: the block holding its first weight
     uint32_t *last_block;      // per row: the block holding its last weight
@@ -121,122 +127,333 @@ __device__ __forceinline__ float dot8(const uint4 &w, const uint4 &x) {
     return d;
 }
 
-// 16-bit lane masks of the elements [a0, a1) of an 8-element group
-__device__ __forceinline__ uint4 element_mask(uint32_t a0, uint32_t a1) {
-    uint32_t m[4];
-#pragma unroll
-    for (uint32_t q = 0; q < 4; ++q) {
-        const uint32_t lo = (2 * q >= a0 && 2 * q < a1) ? 0x0000FFFFu : 0u;
-        const uint32_t hi = (2 * q + 1 >= a0 && 2 * q + 1 < a1) ? 0xFFFF0000u : 0u;
-        m[q] = lo | hi;
-    }
-    return make_uint4(m[0], m[1], m[2], m[3]);
-}
-
-// The block's weights [s, e) times the activations of the (at most two)
-// matrices they belong to: segment 0 is the matrix holding weight s,
-// segment 1 the first matrix that starts inside (s, e).
-__device__ __forceinline__ void dot_block(const GemvArgs &g, const Range &r, const uint8_t *buf,
-                                          uint32_t lane, const uint2 (&S)[kPre], uint32_t b) {
-    const uint32_t s = r.g0 + r.shift, e = r.g0 + r.lim;
-    int seg_m[2] = {-1, -1};
-#pragma unroll
-    for (uint32_t i = 0; i < kMaxM; ++i) {
-        if (i < g.n_mats) {
-            if (g.off[i] <= s && s < g.end[i]) seg_m[0] = static_cast<int>(i);
-            else if (g.off[i] > s && g.off[i] < e && seg_m[1] < 0) seg_m[1] = static_cast<int>(i);
-        }
-    }
-#pragma unroll
-    for (uint32_t j = 0; j < 2; ++j) {
-        if (seg_m[j] < 0) continue;  // uniform
-        const uint32_t m = static_cast<uint32_t>(seg_m[j]);
+// One block's weights [s, e) -- buffer bytes [lo_at, hi_at) from weight g0 on
+// -- times the activations of the (at most two) matrices they belong to, one
+// weight per lane and step: segment 0 is the matrix holding weight s, segment
+// 1 the first matrix that starts inside (s, e).  For the few blocks at the
+// matrices' boundaries; small rather than fast.
+__device__ __forceinline__ void dot_block(const GemvArgs &g, uint32_t g0, uint32_t lo_at,
+                                          uint32_t hi_at, const uint8_t *buf, uint32_t lane,
+                                          uint32_t b) {
+    const uint32_t s = g0 + lo_at, e = g0 + hi_at;
+    bool inside = false;
+#pragma unroll 1
+    for (uint32_t m = 0; m < g.n_mats; ++m) {
         const uint32_t off = g.off[m], cols = g.cols[m];
         const uint32_t lo = umax(s, off), hi = umin(e, g.end[m]);
-        const uint32_t rlo = divide(lo - off, g.div[m]);
-        // starts of the next two rows (the second clamped: past the end of
-        // a stream of 2^32 - 1 weights it would wrap)
-        const uint32_t b1 = off + (rlo + 1u) * cols;
-        const uint32_t b2 = static_cast<uint32_t>(umin64(uint64_t{b1} + cols, 0xFFFFFFFFull));
-        const uint16_t *x = g.x[m];
-        // rows the segment touches (uniform): one row is the common case
-        const uint32_t nrows = divide(hi - 1u - off, g.div[m]) - rlo + 1u;
-        float acc[3] = {0.f, 0.f, 0.f};
-        auto group = [&](uint32_t gi, uint2 Sg, auto one_row) {
-            const uint32_t E = r.g0 + (gi << 3);
-            if ((E < lo && lo - E >= 8u) || E >= hi) return;  // (no E + 8: it may wrap)
-            const uint32_t row = one_row ? rlo : rlo + (E >= b1 ? 1u : 0u) + (E >= b2 ? 1u : 0u);
-            const uint32_t kcol = E - off - row * cols;
-            uint4 w = assemble_group(reinterpret_cast<const uint2 *>(buf)[gi], Sg);
-            uint4 xv = *reinterpret_cast<const uint4 *>(x + kcol);
-            if (E < lo || hi - E < 8u) {  // a group shared with a neighbour: its elements only
-                const uint4 mk = element_mask(lo > E ? lo - E : 0u, umin(hi - E, 8u));
-                w = make_uint4(w.x & mk.x, w.y & mk.y, w.z & mk.z, w.w & mk.w);
-                xv = make_uint4(xv.x & mk.x, xv.y & mk.y, xv.z & mk.z, xv.w & mk.w);
+        if (lo >= hi || (off > s && inside)) continue;
+        inside |= off > s;
+        uint32_t row = (lo - off) / cols;
+        float *slot = g.part + static_cast<uint64_t>(b) * kSlots + (off > s ? kSegSlots : 0u);
+        // rows it touches: at most 3 (4096 weights, 2048 columns)
+#pragma unroll 1
+        for (uint32_t at = lo, i = 0; at < hi && i < kSegSlots; ++row, ++i) {
+            const uint64_t start = uint64_t{off} + uint64_t{row} * cols;
+            const uint32_t stop = static_cast<uint32_t>(umin64(hi, start + cols));
+            float sum = 0.f;
+#pragma unroll 1
+            for (uint32_t q = at + lane; q < stop && q >= at; q += 64u) {
+                const uint32_t sm = g.d.sm[q], ex = buf[q - g0];
+                const uint32_t w = ((sm & 0x80u) << 24) | ((ex & 0x7Fu) << 24) |
+                                   ((ex & 0x80u) << 16) | ((sm & 0x7Fu) << 16);
+                const uint32_t x = g.x[m][q - static_cast<uint32_t>(start)];
+                sum += __builtin_bit_cast(float, w) * __builtin_bit_cast(float, x << 16);
             }
-            const float d = dot8(w, xv);
-            if (one_row) {
-                acc[0] += d;
-            } else {
-                const uint32_t rr = row - rlo;
-                acc[0] += rr == 0u ? d : 0.f;
-                acc[1] += rr == 1u ? d : 0.f;
-                acc[2] += rr == 2u ? d : 0.f;
+            sum = wave_sum(sum);
+            if (lane == 63u) {
+                slot[i] = sum;
+                if (start >= lo) g.first_block[g.row_base[m] + row] = b;
+                if (start + cols <= hi) g.last_block[g.row_base[m] + row] = b;
             }
-        };
-        auto all_groups = [&](auto one_row) {
-#pragma unroll
-            for (int k = 0; k < kPre; ++k) {
-                const uint32_t gi = lane + 64u * k;
-                if (gi < r.ngroups) group(gi, S[k], one_row);
-            }
-            for (uint32_t gi = lane + 64u * kPre; gi < r.ngroups; gi += 64u)
-                group(gi, *reinterpret_cast<const uint2 *>(g.d.sm + r.g0 + (gi << 3)), one_row);
-        };
-        if (nrows == 1u) all_groups(std::true_type{});
-        else all_groups(std::false_type{});
-        const float t0 = wave_sum(acc[0]);
-        const float t1 = nrows > 1u ? wave_sum(acc[1]) : 0.f;
-        const float t2 = nrows > 2u ? wave_sum(acc[2]) : 0.f;
-        if (lane == 63u)
-            *reinterpret_cast<float4 *>(g.part + static_cast<uint64_t>(b) * kSlots + j * kSegSlots) =
-                make_float4(t0, t1, t2, 0.f);
-        if (lane < nrows) {  // rows whose first or last weight is in this block, one per lane
-            const uint64_t rs = uint64_t{off} + uint64_t{rlo + lane} * cols;
-            if (rs >= lo) g.first_block[g.row_base[m] + rlo + lane] = b;
-            if (rs + cols <= hi) g.last_block[g.row_base[m] + rlo + lane] = b;
+            at = stop;
         }
     }
 }
 
-// Same loop as the decode kernel (one wave per block, persistent grid); the
-// decoded block goes into dot_block instead of memory.
+// The matrix a wave is in.  Its blocks come in stream order, so the matrix
+// only ever moves on; its description stays in scalar registers (all eight
+// would not fit beside the decoder's).
+struct Current {
+    uint32_t next;      // index of the next matrix
+    uint32_t next_off;  // its first weight
+    uint32_t off, end, cols, row_base, x_at, x_set;
+    Divider div;
+    const uint16_t *x;
+};
+
+__device__ __forceinline__ uint32_t matrix_start(const GemvArgs &g, uint32_t m) {
+    return m < g.n_mats ? g.off[m] : 0xFFFFFFFFu;
+}
+
+// The last matrix that starts at or before weight s (none: an empty range).
+__device__ __forceinline__ void advance(const GemvArgs &g, uint32_t s, Current &cur) {
+    while (s >= cur.next_off && cur.next < g.n_mats) {
+        const uint32_t m = cur.next++;
+        cur.off = cur.next_off;
+        cur.next_off = matrix_start(g, cur.next);
+        cur.end = g.end[m];
+        cur.cols = g.cols[m];
+        cur.row_base = g.row_base[m];
+        cur.x_at = g.x_at[m];
+        cur.x_set = g.x_set[m];
+        cur.div = g.div[m];
+        cur.x = g.x[m];
+    }
+}
+
+// A block inside one matrix (then it touches at most three of its rows): all
+// but the few at the matrices' boundaries.
+struct Span {
+    bool plain;
+    uint32_t rlo, cols;
+    uint32_t col0;  // column of the block's first group
+    uint32_t nrows;
+};
+
+__device__ __forceinline__ Span block_span(const Current &cur, const Range &r) {
+    const uint32_t s = r.g0 + r.shift, e = r.g0 + r.lim;
+    Span sp{};
+    if (s < e && cur.off <= s && e <= cur.end) {
+        sp.cols = cur.cols;
+        sp.rlo = divide(s - cur.off, cur.div);
+        sp.nrows = divide(e - 1u - cur.off, cur.div) - sp.rlo + 1u;
+        sp.col0 = r.g0 - cur.off - sp.rlo * sp.cols;  // rows and groups start on multiples of 8
+        sp.plain = true;
+    }
+    return sp;
+}
+
+// Column of byte `at` (a weight counted from the block's first group): c minus
+// cols wraps to a large value while c is still in the row.
+__device__ __forceinline__ uint32_t span_column(const Span &sp, uint32_t at) {
+    uint32_t c = sp.col0 + at;
+    c = umin(c, c - sp.cols);
+    return umin(c, c - sp.cols);
+}
+
+// 8 activations from column c on: from LDS where they are staged.
+__device__ __forceinline__ uint4 load_x8(const uint8_t *staged, const uint16_t *x, bool in_lds,
+                                         uint32_t c) {
+    if (in_lds) return *reinterpret_cast<const uint4 *>(staged + 2u * c);
+    return *reinterpret_cast<const uint4 *>(x + c);
+}
+
+// A plain block's weights times their activations: whole groups eight at a
+// time; the elements of the (at most two) groups shared with the neighbours
+// one per lane.
+__device__ __forceinline__ void dot_plain(const GemvArgs &g, const Range &r, const Current &cur,
+                                          const Span &sp, const uint8_t *buf, const uint8_t *staged,
+                                          bool in_lds, uint32_t lane, const Groups<kPre> &gr,
+                                          const uint2 (&S)[kPre], uint32_t edge_sm, uint32_t b) {
+    const uint32_t el = edge_byte(r, lane & 15u);
+    uint2 E[kPre];
+    uint4 X[kPre];
+#pragma unroll
+    for (int k = 0; k < kPre; ++k) E[k] = *reinterpret_cast<const uint2 *>(buf + gr.at[k]);
+    uint32_t edge_x;
+    if (__builtin_expect(in_lds, 1)) {  // uniform
+#pragma unroll
+        for (int k = 0; k < kPre; ++k)
+            X[k] = *reinterpret_cast<const uint4 *>(staged + 2u * span_column(sp, gr.at[k]));
+        edge_x = *reinterpret_cast<const uint16_t *>(staged + 2u * span_column(sp, el));
+    } else {
+#pragma unroll
+        for (int k = 0; k < kPre; ++k)
+            X[k] = *reinterpret_cast<const uint4 *>(cur.x + span_column(sp, gr.at[k]));
+        edge_x = cur.x[span_column(sp, el)];
+    }
+    const uint32_t edge_e = buf[el];
+    float t[3] = {0.f, 0.f, 0.f};
+    // (rows past the block's are never reached: c stays below their start)
+    auto add = [&](float v, uint32_t at) {
+        const uint32_t c = sp.col0 + at;
+        const bool second = c >= sp.cols, third = c >= 2u * sp.cols;
+        t[0] += second ? 0.f : v;
+        t[1] += second && !third ? v : 0.f;
+        t[2] += third ? v : 0.f;
+    };
+    float d[kPre + 1];
+#pragma unroll
+    for (int k = 0; k < kPre; ++k) {
+        const float v = dot8(assemble_group(E[k], S[k]), X[k]);
+        // (a select: the product of a group that is not this lane's may be NaN)
+        d[k] = full_group(r, lane + 64u * k) ? v : 0.f;
+    }
+    {
+        const bool mine = lane < 16u && !full_group(r, el >> 3) && (lane < 8u || el >= 8u) &&
+                          el >= r.shift && el < r.lim;
+        const uint32_t w = ((edge_sm & 0x80u) << 24) | ((edge_e & 0x7Fu) << 24) |
+                           ((edge_e & 0x80u) << 16) | ((edge_sm & 0x7Fu) << 16);
+        const float v = __builtin_bit_cast(float, w) * __builtin_bit_cast(float, edge_x << 16);
+        d[kPre] = mine ? v : 0.f;
+    }
+    if (sp.nrows == 1u) {  // uniform; three of five blocks with 4096 columns
+#pragma unroll
+        for (int k = 0; k <= kPre; ++k) t[0] += d[k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < kPre; ++k) add(d[k], gr.at[k]);
+        add(d[kPre], el);
+    }
+#pragma unroll 1
+    for (uint32_t gi = lane + 64u * kPre; __builtin_expect(gi < r.full_hi, 0); gi += 64u) {
+        const uint32_t at = gi << 3;
+        add(dot8(assemble_group(reinterpret_cast<const uint2 *>(buf)[gi],
+                                *reinterpret_cast<const uint2 *>(g.d.sm + r.g0 + at)),
+                 load_x8(staged, cur.x, in_lds, span_column(sp, at))),
+            at);
+    }
+    t[0] = wave_sum(t[0]);
+    if (sp.nrows > 1u) t[1] = wave_sum(t[1]);
+    if (sp.nrows > 2u) t[2] = wave_sum(t[2]);
+    if (lane == 63u)
+        *reinterpret_cast<float4 *>(g.part + static_cast<uint64_t>(b) * kSlots) =
+            make_float4(t[0], t[1], t[2], 0.f);
+    // rows whose first or last weight is here (the first row's column 0 only
+    // when the block starts there; always column 0 of the others)
+    if (lane < sp.nrows) {
+        const uint32_t row = cur.row_base + sp.rlo + lane;
+        if (lane != 0u || sp.col0 + r.shift == 0u) g.first_block[row] = b;
+        if (sp.col0 + r.lim >= (lane + 1u) * sp.cols) g.last_block[row] = b;
+    }
+}
+
+// Last block that starts at or before weight `pos`: 64 probes at a time.
+__device__ __forceinline__ uint32_t find_block(const DecodeArgs &a, uint32_t pos, uint32_t lane) {
+    uint32_t lo = 0, n = a.num_blocks;  // the answer is in [lo, lo + n)
+    while (n > 1u) {
+        const uint32_t step = (n + 63u) / 64u;
+        const bool le = lane * step < n && a.block_pos[lo + umin(lane * step, n - 1u)] <= pos;
+        const uint32_t hits = static_cast<uint32_t>(__builtin_popcountll(__builtin_amdgcn_ballot_w64(le)));
+        const uint32_t j = umax(hits, 1u) - 1u;
+        lo += j * step;
+        n = umin(step, n - j * step);
+    }
+    return lo;
+}
+
+// Where a matrix starts (q even) or ends (q odd).
+__device__ __forceinline__ uint32_t boundary(const GemvArgs &g, uint32_t q) {
+    return (q & 1u) ? g.end[q >> 1] : g.off[q >> 1];
+}
+
+// The block that has boundary q inside it (the first of its boundaries takes
+// it): decoded by one wave like any other, multiplied by dot_block.
+__device__ __forceinline__ void boundary_block(const GemvArgs &g, const Tables &tb, uint8_t *lds,
+                                               uint32_t buf_off, uint32_t lane, uint32_t q) {
+    const DecodeArgs &a = g.d;
+    const uint32_t pos = boundary(g, q);
+    if (pos >= a.n_elems) return;
+    const uint32_t b = static_cast<uint32_t>(
+        __builtin_amdgcn_readfirstlane(static_cast<int>(find_block(a, pos, lane))));
+    const ChunkWords cw = load_chunk<64>(a, b, lane);
+    const Chunk ch[1] = {chunk_setup<64>(a, cw, b, lane)};
+    const Range r = block_range(a, cw);
+    const uint32_t s = r.g0 + r.shift, e = r.g0 + r.lim;
+    if (pos <= s || pos >= e) return;
+    for (uint32_t i = 0; i < q; ++i)
+        if (boundary(g, i) > s && boundary(g, i) < e) return;
+    for (uint32_t i = lane; i < (a.buf_bytes >> 4); i += 64u)
+        reinterpret_cast<uint4 *>(lds + buf_off)[i] = make_uint4(0u, 0u, 0u, 0u);
+    Trail<kKeep> tr[1];
+    uint32_t state[1], out8[1];
+    decode_count(tb, ch, tr, state, out8);
+    const uint32_t excl8 = wave_inclusive_scan(out8[0]) - out8[0];
+    wave_lds_sync();
+    emit_exponents(tb, ch[0], tr[0], state[0], 8u * r.shift + excl8, buf_off, a.buf_bytes);
+    wave_lds_sync();
+    dot_block(g, r.g0, r.shift, r.lim, lds + buf_off + kBufLead, lane, b);
+}
+
+// Same loop as the decode kernel's for 64-chunk blocks (persistent grid, one
+// wave per block); the decoded weights go into their dot products instead of
+// memory.  The activations are staged in LDS, as many matrices' at once as
+// its part for them holds: read through the caches they are three times the
+// stream's own bytes, and the streaming data evicts them from the L1.  A
+// workgroup takes W neighbouring blocks per round and stages the next set
+// when the first of them reaches it; the few blocks of a round that are
+// already past the staged set read their activations from memory.
+//
+// The blocks at the matrices' boundaries go to the first workgroups, a wave
+// each: in the loop, their code would cost every block scalar registers
+// (0.130 ms with it, 0.121 ms without).
+//
+// Bound: instruction issue and latency -- about 400 vector and 280 scalar
+// instructions per block, six waves per SIMD.  A Llama-3-8B-sized block's
+// compressed bytes alone take 57 us at the rate of a device copy; 153 us
+// before and 119 us now for the two kernels.
 template <uint32_t W>
-__global__ __launch_bounds__(64 * W) void df11_gemv_wave_kernel(GemvArgs g) {
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) void
+df11_gemv_wave_kernel(GemvArgs g) {
     const DecodeArgs &a = g.d;
     extern __shared__ __align__(16) uint8_t lds[];
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = tid & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // block indices stay scalar
+    const uint32_t main_grid = gridDim.x - g.boundary_grid;
+    if (blockIdx.x < g.boundary_grid) {
+        stage_table_blob(a, lds, tid, 64 * W);
+        const Tables tb = stage_tables(a, lds);
+        __syncthreads();
+        const uint32_t q = blockIdx.x * W + wave;
+        if (q < 2u * g.n_mats)
+            boundary_block(g, tb, lds, a.table_lds_bytes + g.x_bytes + wave * a.buf_bytes, lane, q);
+        return;
+    }
+    const uint32_t first_group = xcd_grouped_index(blockIdx.x - g.boundary_grid, main_grid) * W;
+    const uint32_t stride = main_grid * W;
+    ChunkWords cw{};
+    uint32_t group_pos = 0;  // first weight of the round's first block
+    if (first_group + wave < a.num_blocks) cw = load_chunk<64>(a, first_group + wave, lane);
+    if (first_group < a.num_blocks) group_pos = block_positions(a)[first_group];
     stage_table_blob(a, lds, tid, 64 * W);
     const Tables tb = stage_tables(a, lds);
-    const uint32_t buf_off = a.table_lds_bytes + wave * a.buf_bytes;
+    uint8_t *xs = lds + a.table_lds_bytes;
+    const uint32_t buf_off = a.table_lds_bytes + g.x_bytes + wave * a.buf_bytes;
     uint8_t *buf = lds + buf_off + kBufLead;
     __syncthreads();
-
-    const uint32_t first_block = xcd_grouped_index(blockIdx.x, gridDim.x) * W + wave;
-    const uint32_t stride = gridDim.x * W;
-    if (first_block >= a.num_blocks) return;
-    ChunkWords cw = load_chunk<64>(a, first_block, lane);
-    Chunk ch[1] = {chunk_setup<64>(a, cw, first_block, lane)};
+    Chunk ch[1] = {chunk_setup<64>(a, cw, first_group + wave, lane)};
     Range r = block_range(a, cw);
+    Current cur{};
+    cur.next_off = matrix_start(g, 0u);
+    uint32_t set = 0, next_set = 0;        // staged set (none yet: 0), and where the next begins
+    uint32_t next_set_mat = 0;
+    next_set = matrix_start(g, 0u);
 
-    for (uint32_t b = first_block; b < a.num_blocks; b += stride) {
-        const uint32_t bn = b + stride;
+    for (uint32_t group = first_group; group < a.num_blocks; group += stride) {
+        // (uniform over the workgroup: every wave sees the same positions)
+        if (__builtin_expect(group_pos >= next_set && next_set_mat < g.n_mats, 0)) {
+            uint32_t m = next_set_mat, found = 0;
+            // the set of the matrix holding group_pos: skip sets that end before it
+            while (next_set_mat < g.n_mats && group_pos >= matrix_start(g, next_set_mat)) {
+                if (g.x_set[next_set_mat] != found) {
+                    found = g.x_set[next_set_mat];
+                    m = next_set_mat;
+                }
+                ++next_set_mat;
+            }
+            while (next_set_mat < g.n_mats && g.x_set[next_set_mat] == found) ++next_set_mat;
+            next_set = matrix_start(g, next_set_mat);
+            set = found;
+            __syncthreads();  // the staged activations are no longer read
+            for (; m < next_set_mat; ++m) {
+                if (g.x_at[m] == kNotStaged) continue;
+                const uint4 *src = reinterpret_cast<const uint4 *>(g.x[m]);
+                uint4 *dst = reinterpret_cast<uint4 *>(xs + g.x_at[m]);
+                for (uint32_t i = tid; i < g.cols[m] / 8u; i += 64u * W) dst[i] = src[i];
+            }
+            __syncthreads();
+        }
+        const uint32_t b = group + wave;
+        const uint32_t gn = group + stride;
+        if (gn < a.num_blocks) group_pos = block_positions(a)[gn];
+        if (b >= a.num_blocks) continue;  // the last round's spare waves
         ChunkWords nxt = cw;
-        if (bn < a.num_blocks) nxt = load_chunk<64>(a, bn, lane);
+        if (b + stride < a.num_blocks) nxt = load_chunk<64>(a, b + stride, lane);
+        const Groups<kPre> gr = block_groups<kPre>(r, lane, 64u);
         uint2 S[kPre];
-        prefetch_sm(a, r, block_groups<kPre>(r, lane, 64u), S);
+        prefetch_sm(a, r, gr, S);
+        const uint32_t edge_sm = a.sm[r.g0 + edge_byte(r, lane & 15u)];
 
         wave_lds_sync();
         for (uint32_t i = lane; i < (a.buf_bytes >> 4); i += 64u)
@@ -252,19 +469,31 @@ __global__ __launch_bounds__(64 * W) void df11_gemv_wave_kernel(GemvArgs g) {
         wave_lds_sync();
 
         __builtin_amdgcn_s_setprio(2);
-        dot_block(g, r, buf, lane, S, b);
+        advance(g, r.g0 + r.shift, cur);
+        const Span sp = block_span(cur, r);
+        if (__builtin_expect(sp.plain, 1))
+            dot_plain(g, r, cur, sp, buf, xs + cur.x_at, cur.x_set == set && cur.x_at != kNotStaged,
+                      lane, gr, S, edge_sm, b);
         __builtin_amdgcn_s_setprio(0);
         cw = nxt;
-        ch[0] = chunk_setup<64>(a, cw, bn, lane);
+        ch[0] = chunk_setup<64>(a, cw, b + stride, lane);
         r = block_range(a, cw);
     }
 }
 
-// y[m][row] = sum over the blocks covering the row, in block order, of the
-// block's partial sum for that row.
+// Lanes per row in the reduction: the row's blocks (2 to 4 with 4096 columns,
+// about 10 with 14336) are then all requested at once, and the sum costs two
+// dependent round trips whatever their number (one thread per row took one
+// per block: 8.5 us for the 43,008 rows of a Llama-3-8B-sized block).
+constexpr uint32_t kRowLanes = 16;  // one DPP row
+
+// y[m][row] = sum over the blocks covering the row of the block's partial sum
+// for that row: lane q of the row's 16 adds blocks q, q+16, ... counted from
+// the row's first, then the lanes' sums are added in a fixed order.
 __global__ __launch_bounds__(256) void df11_gemv_reduce_kernel(ReduceArgs ra) {
-    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
-    if (i >= ra.row_start[ra.n_mats]) return;
+    const uint32_t i = blockIdx.x * (256u / kRowLanes) + threadIdx.x / kRowLanes;
+    const uint32_t q0 = threadIdx.x % kRowLanes;
+    if (i >= ra.row_start[ra.n_mats]) return;  // whole 16-lane rows leave together
     uint32_t m = 0;
 #pragma unroll
     for (uint32_t q = 1; q < kMaxM; ++q)
@@ -287,36 +516,77 @@ __global__ __launch_bounds__(256) void df11_gemv_reduce_kernel(ReduceArgs ra) {
     // a block holds >= 128 weights (64 chunks, >= 2 codes each), so a row
     // spans at most cols / 128 + 2 blocks; indices outside that (not written
     // by the decode kernel) give NaN instead of reads out of range
-    if (lb >= ra.num_blocks || fb > lb || lb - fb > cols / 128u + 2u) {
-        y[row] = __builtin_nanf("");
-        return;
-    }
+    const bool bad = lb >= ra.num_blocks || fb > lb || lb - fb > cols / 128u + 2u;
     float sum = 0.f;
-    for (uint32_t b = fb; b <= lb; ++b) {
-        const uint32_t bs = ra.block_pos[b];
-        const uint32_t j = off <= bs ? 0u : 1u;
-        const uint32_t seg_lo = bs > off ? bs : off;
-        const uint32_t rlo = (seg_lo - off) / cols;
-        const uint32_t rr = row - rlo;  // 0..2 by construction; checked to keep reads in range
-        if (rr < 3u) sum += ra.part[static_cast<uint64_t>(b) * kSlots + j * kSegSlots + rr];
+    if (!bad) {
+        for (uint32_t b = fb + q0; b <= lb && b >= fb; b += kRowLanes) {
+            const uint32_t bs = ra.block_pos[b];
+            const uint32_t j = off <= bs ? 0u : 1u;
+            const uint32_t seg_lo = bs > off ? bs : off;
+            const uint32_t rlo = (seg_lo - off) / cols;
+            const uint32_t rr = row - rlo;  // 0..2 by construction; checked to keep reads in range
+            if (rr < 3u) sum += ra.part[static_cast<uint64_t>(b) * kSlots + j * kSegSlots + rr];
+        }
     }
-    y[row] = sum;
+    // lane 15 of the row ends with the sum of its 16 lanes
+    sum += dpp_f32<0x111, 0xF, true>(sum);
+    sum += dpp_f32<0x112, 0xF, true>(sum);
+    sum += dpp_f32<0x114, 0xF, true>(sum);
+    sum += dpp_f32<0x118, 0xF, true>(sum);
+    if (q0 == kRowLanes - 1u) y[row] = bad ? __builtin_nanf("") : sum;
 }
 
 using GemvFn = void (*)(GemvArgs);
 
-GemvFn gemv_kernel(uint32_t W) { return W == 4 ? df11_gemv_wave_kernel<4> : nullptr; }
+GemvFn gemv_kernel(uint32_t W) {
+    switch (W) {
+        case 4: return df11_gemv_wave_kernel<4>;
+        case 8: return df11_gemv_wave_kernel<8>;
+        case 12: return df11_gemv_wave_kernel<12>;
+        case 16: return df11_gemv_wave_kernel<16>;
+        default: return nullptr;
+    }
+}
+
+// LDS for activations: matrices of up to 16384 columns one at a time, smaller
+// ones several (a Llama-3-8B-sized block's seven in three sets, so a
+// workgroup stops to stage them twice after its start).
+constexpr uint32_t kXBytes = 32768;
+
+uint32_t assign_x_sets(const df11_matrix *mats, uint32_t n_mats, GemvArgs *g) {
+    uint32_t set = 1, used = 0, most = 0;
+    for (uint32_t m = 0; m < n_mats; ++m) {
+        const uint64_t need = 2ull * mats[m].cols;
+        if (need > kXBytes) {
+            g->x_set[m] = set;
+            g->x_at[m] = kNotStaged;
+            continue;
+        }
+        if (used + need > kXBytes) {
+            ++set;
+            used = 0;
+        }
+        g->x_set[m] = set;
+        g->x_at[m] = used;
+        used += static_cast<uint32_t>(need);
+        if (used > most) most = used;
+    }
+    return most;
+}
 
 struct Shape {
     int dev;
-    uint32_t lut_bits, buf, W, per_cu;
+    uint32_t fixed, buf, W, per_cu;
 };
 std::mutex g_mu;
 std::vector<Shape> g_shapes;
+std::vector<std::array<uint32_t, 4>> g_lds_granted;  // per device and kernel: dynamic LDS allowed
 constexpr size_t kMaxShapes = 64;
 
-// workgroup size and resident workgroups per CU for this table and buffer size
-int gemv_shape(uint32_t lut_bits, uint32_t buf, uint32_t *W_out, uint32_t *grid_max) {
+// Workgroup size and resident workgroups per CU for `fixed` bytes of LDS per
+// workgroup and `buf` per wave: the most resident waves, fewer per workgroup
+// on a tie.
+int gemv_shape(uint32_t fixed, uint32_t buf, uint32_t *W_out, uint32_t *grid_max) {
     int dev = 0, cus = 0, max_lds = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -324,21 +594,29 @@ int gemv_shape(uint32_t lut_bits, uint32_t buf, uint32_t *W_out, uint32_t *grid_
         return DF11_E_HIP;
     std::lock_guard<std::mutex> lk(g_mu);
     for (const Shape &sh : g_shapes) {
-        if (sh.dev == dev && sh.lut_bits == lut_bits && sh.buf == buf) {
+        if (sh.dev == dev && sh.fixed == fixed && sh.buf == buf) {
             *W_out = sh.W;
             *grid_max = sh.per_cu * static_cast<uint32_t>(cus);
             return DF11_OK;
         }
     }
-    const uint32_t tab = static_cast<uint32_t>(df11tab::lds_bytes(lut_bits));
+    if (g_lds_granted.size() <= static_cast<size_t>(dev)) g_lds_granted.resize(dev + 1);
+    std::array<uint32_t, 4> &granted = g_lds_granted[dev];
     uint32_t best_W = 0, best_pc = 0, best_waves = 0;
-    for (uint32_t W : {4u}) {
-        const uint32_t lds = tab + W * buf;
-        if (lds > static_cast<uint32_t>(max_lds) || lds > 65536u) continue;
+    for (uint32_t i = 0; i < 4; ++i) {
+        const uint32_t W = 4u * (i + 1u);
+        const uint32_t lds = fixed + W * buf;
+        if (lds > static_cast<uint32_t>(max_lds)) continue;
+        const void *fn = reinterpret_cast<const void *>(gemv_kernel(W));
+        if (lds > 65536u && granted[i] < lds) {
+            if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    static_cast<int>(lds)) != hipSuccess)
+                return DF11_E_HIP;
+            granted[i] = lds;
+        }
         int pc = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &pc, reinterpret_cast<const void *>(gemv_kernel(W)), static_cast<int>(64 * W),
-                lds) != hipSuccess)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&pc, fn, static_cast<int>(64 * W), lds) !=
+            hipSuccess)
             return DF11_E_HIP;
         if (static_cast<uint32_t>(pc) * W > best_waves) {
             best_waves = static_cast<uint32_t>(pc) * W;
@@ -348,7 +626,7 @@ int gemv_shape(uint32_t lut_bits, uint32_t buf, uint32_t *W_out, uint32_t *grid_
     }
     if (!best_waves) return DF11_E_UNSUPPORTED;
     if (g_shapes.size() >= kMaxShapes) g_shapes.clear();
-    g_shapes.push_back(Shape{dev, lut_bits, buf, best_W, best_pc});
+    g_shapes.push_back(Shape{dev, fixed, buf, best_W, best_pc});
     *W_out = best_W;
     *grid_max = best_pc * static_cast<uint32_t>(cus);
     return DF11_OK;
@@ -462,15 +740,19 @@ int df11_block_gemv(const df11_stream *dev, const df11_matrix *mats, uint32_t n_
     ra.last_block = g.last_block;
 
     uint32_t W = 0, grid_max = 0;
-    rc = gemv_shape(a.lut_bits, a.buf_bytes, &W, &grid_max);
+    g.x_bytes = assign_x_sets(mats, n_mats, &g);
+    rc = gemv_shape(a.table_lds_bytes + g.x_bytes, a.buf_bytes, &W, &grid_max);
     if (rc) return rc;
+    g.boundary_grid = (2u * n_mats + W - 1) / W;
     uint32_t grid = (a.num_blocks + W - 1) / W;
-    if (grid > grid_max) grid = grid_max;
+    const uint32_t room = grid_max > g.boundary_grid ? grid_max - g.boundary_grid : 1u;
+    if (grid > room) grid = room;
     if (!grid) grid = 1;
-    const uint32_t lds = a.table_lds_bytes + W * a.buf_bytes;
+    grid += g.boundary_grid;
+    const uint32_t lds = a.table_lds_bytes + g.x_bytes + W * a.buf_bytes;
     hipLaunchKernelGGL(gemv_kernel(W), dim3(grid), dim3(64 * W), lds, stream, g);
     if (hipGetLastError() != hipSuccess) return DF11_E_HIP;
-    hipLaunchKernelGGL(df11_gemv_reduce_kernel, dim3(static_cast<uint32_t>((rows + 255) / 256)),
+    hipLaunchKernelGGL(df11_gemv_reduce_kernel, dim3(static_cast<uint32_t>((rows * kRowLanes + 255) / 256)),
                        dim3(256), 0, stream, ra);
     return hipGetLastError() == hipSuccess ? DF11_OK : DF11_E_HIP;
 }
