@@ -6,24 +6,27 @@
 // With at most 64 activation rows the products are bound by streaming the
 // weights from HBM, so the design reads every weight once, with 16-byte
 // loads, and keeps several kilobytes in flight per wave:
-//   - one wavefront computes a tile of 16 output features x all tokens over a
-//     contiguous range of k; all matrices of the block share one launch;
+//   - all matrices of the block share one launch; a wavefront computes tiles of
+//     16 output features x all tokens over ranges of k;
 //   - per 64 k a lane feeds 2 x 8 BF16 of one weight row (lanes 16g..16g+15
 //     take rows 0..15 at k offset 16g) and the matching activations to
 //     v_mfma_f32_16x16x32_bf16, twice per 16-token slice; A (tokens) and B
 //     (features) use the same assignment of k to lanes, so the dot products
 //     cover each k once whatever order the unit sums in;
-//   - up to 3 tokens each wave loads its weights straight into that layout
-//     and reads its activations from memory; from 4, a workgroup of 4 waves
-//     stages each 256-k activation slab in LDS once, and each wave passes
-//     its weights through LDS so that every load reads whole cache lines;
-//   - a matrix is split into k ranges of about 1024 columns (up to 8
-//     tokens) or 4096 columns, or half that where it evens out the work per
-//     CU (more tokens); each range of a split matrix writes fp32 partial
-//     sums, and a second kernel adds them in a fixed order, so results are
-//     deterministic (no atomics).
+//   - each wave passes its weights through LDS of its own, so that every load
+//     reads whole cache lines;
+//   - up to 16 tokens a workgroup of 4 waves holds whole rows: the waves take
+//     k ranges of 1024 columns in turn, with the activations in LDS too, and
+//     add their totals in LDS;
+//   - from 17 tokens the 4 waves of a workgroup cover 64 features over one k
+//     range and share each 256-k activation slab in LDS; a matrix is split
+//     into ranges of about 4096 columns, or half that where it evens out the
+//     work per CU, each range of a split matrix writes fp32 partial sums, and
+//     a second kernel adds them in a fixed order.
+// Results are deterministic (no atomics).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <mutex>
 #include <vector>
@@ -39,15 +42,15 @@ constexpr uint32_t kTileRows = 16;   // output features per wave
 constexpr uint32_t kKStep = 64;      // k per inner step: two MFMAs
 constexpr uint32_t kUnroll = 4;      // inner steps whose weight loads are issued together
 constexpr uint32_t kKPerIter = kKStep * kUnroll;
-// k range of one wave before a matrix is split: short ranges (more
-// workgroups in flight) pay off while the products are light; from 9
-// tokens the products per weight favour long ranges (whose weights pass
-// through LDS), and the split is chosen to balance the CUs
+// k range of one wave of the rows kernel, and of one workgroup from 17 tokens
+// (there the split is chosen to balance the CUs).  The workspace up to 8
+// tokens is still counted in ranges of kKTargetFew, so that a caller's sizes
+// and what is refused stay what they were; nothing is written there.
 constexpr uint32_t kKTargetFew = 1024;
 constexpr uint32_t kKTargetMany = 4096;
 constexpr uint32_t kFewTokens = 8;
-constexpr uint32_t kSlabMinTokens = 4;  // fewer tokens: activations straight from memory
-constexpr uint32_t kWaves = 4;       // waves per workgroup, up to 3 tokens
+constexpr uint32_t kRowsTokens = 16;  // tokens up to which the rows kernel runs
+constexpr uint32_t kWaves = 4;       // waves per workgroup, up to 16 tokens
 constexpr uint32_t kSlabWaves = 4;   // waves per workgroup sharing one activation slab
 constexpr uint32_t kMax = DF11_MAX_MATRICES;
 
@@ -56,10 +59,8 @@ struct GemmArgs {
     float *part;
     uint32_t n_mats;
     uint32_t tokens;
-    uint32_t num_tiles;
     uint32_t num_wg;
-    uint32_t tile_start[kMax + 1];  // prefix sums of 16-feature tiles per matrix
-    uint32_t wg_start[kMax + 1];    // prefix sums of 64-feature workgroup tiles
+    uint32_t wg_start[kMax + 1];    // prefix sums of workgroups per matrix
     uint32_t ksplit[kMax];          // k ranges per matrix
     uint32_t kchunk[kMax];          // k per range (multiple of kKPerIter)
     uint32_t rows[kMax];
@@ -151,52 +152,147 @@ __device__ __forceinline__ void write_tile(const GemmArgs &a, const Mat &m, uint
 // half h gives lane group g the 8 values kk + 32h + 8g .. +7, so the four
 // lanes of one row read 64 contiguous bytes per load.
 
-// Up to 3 tokens: one wavefront per 16-feature tile, activations read
-// straight from memory (a few hundred bytes per k range, cache resident).
-__global__ __launch_bounds__(64 * kWaves) void gemm_tiles_kernel(GemmArgs a) {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t tile =
-        blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (tile >= a.num_tiles) return;
+// Up to 16 tokens: one workgroup per 16 features and all of k.  Wave w takes
+// the k ranges w, w + 4, ... one after the other, each summed from zero (as
+// long a chain of roundings as a range, whatever the matrix) and added to the
+// wave's total; the four totals meet in LDS, in wave order.  No partial sums go
+// through memory and no second kernel adds them.  A token's row of the matrix
+// unit depends on that token's activations alone, so rows past the last token
+// repeat it and are not written.
+//
+// Weights and activations pass through LDS of the wave's own: a load
+// instruction reads 512 contiguous bytes of each of two rows (8 whole cache
+// lines) rather than 64 bytes of each of 16 rows, and nothing needs a barrier,
+// since one wave's LDS accesses complete in order.  Row r's 16-byte piece p of
+// the weights lies at slot (p + r) mod 32 and the activation rows are padded by
+// 16 bytes, so reads have no bank conflicts.
+//
+// Bound: the weight stream.  Seven matrices of a Llama-3-8B-sized block, us,
+// before (a workgroup per range of k and a kernel that adds them; up to 3
+// tokens operands straight from memory) and now: 1 token 77.2 and 72.8, 3
+// tokens 83.9 and 73.3, 5 tokens 82.8 and 73.6, 9 tokens 83.8 and 74.3, 16
+// tokens 84.7 and 81.4 (70B-sized 351 and 292).  From 17 tokens four waves'
+// own activations no longer fit the LDS beside each other.
+constexpr uint32_t kRowsXStride = kKPerIter * 2 + 16;       // bytes per row in LDS
+constexpr uint32_t kRowsW = kTileRows * kKPerIter * 2;      // one wave's weight slab
+template <uint32_t XR>  // activation rows staged: 8 or 16
+constexpr uint32_t kRowsLds = kRowsW + XR * kRowsXStride;
+
+template <uint32_t XR>
+__global__ __launch_bounds__(64 * kWaves) void gemm_rows_kernel(GemmArgs a) {
+    typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kWaves * kRowsLds<XR>];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t lane = tid & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     uint32_t first;
-    const Mat m = select_matrix(a, a.tile_start, tile, &first);
-    const uint32_t local = tile - first;
-    const uint32_t rb = local / m.ksplit;
-    const uint32_t s = local - rb * m.ksplit;
-    const uint32_t k0 = s * m.kchunk;
-    const uint32_t k1 = umin(m.cols, k0 + m.kchunk);
-
-    const uint32_t j = lane & 15u;   // feature row (B) / token row (A) in the slice
+    const Mat m = select_matrix(a, a.wg_start, blockIdx.x, &first);
+    const uint32_t rb = blockIdx.x - first;
+    const uint32_t j = lane & 15u;   // feature row (B) / token row (A)
     const uint32_t g = lane >> 4;    // k group
-    const uint16_t *wrow = a.w + m.w_off + static_cast<uint64_t>(rb * kTileRows + j) * m.cols + 8u * g;
-    // rows of x past the last token read token 0 and are masked to zero
-    const uint32_t xmask = j < a.tokens ? ~0u : 0u;
-    const uint16_t *xrow = m.x + static_cast<uint64_t>(j < a.tokens ? j : 0u) * m.cols + 8u * g;
+    const uint16_t *w = a.w + m.w_off + static_cast<uint64_t>(rb * kTileRows) * m.cols;
+    f32x4 total = {0.f, 0.f, 0.f, 0.f};
 
-    f32x4 acc[1] = {f32x4{0.f, 0.f, 0.f, 0.f}};
-    auto step = [&](uint32_t kk, uint4 w0, uint4 w1) {
-        const uint4 x0 = masked(load16(xrow + kk), xmask);
-        const uint4 x1 = masked(load16(xrow + kk + 32u), xmask);
-        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(x0), as_bf16x8(w0), acc[0], 0, 0, 0);
-        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(x1), as_bf16x8(w1), acc[0], 0, 0, 0);
+    const uint32_t half = lane >> 5, pl = lane & 31u;
+    uint8_t *mine = lds + wave * kRowsLds<XR>;
+    u32x4v *wl = reinterpret_cast<u32x4v *>(mine);
+    uint8_t *xl = mine + kRowsW;
+    const uint16_t *wrow2 = w + static_cast<uint64_t>(half) * m.cols;
+    u32x4v W[8], X[XR / 2];
+    // 16-byte piece of the slab at k that this lane loads (pieces past the
+    // range repeat its last one)
+    auto piece = [&](uint32_t k, uint32_t k1) {
+        return k + 8u * umin(pl, umin(32u, (k1 - k) / 8u) - 1u);
     };
-    uint32_t k = k0;
-    for (; k + kKPerIter <= k1; k += kKPerIter) {
-        // the weight loads of kUnroll steps are issued before their products
-        uint4 W[kUnroll][2];
+    auto load_w = [&](uint32_t i, uint32_t at) {
+        W[i] = *reinterpret_cast<const u32x4v *>(wrow2 + static_cast<uint64_t>(2u * i) * m.cols + at);
+    };
+    auto load_x = [&](uint32_t at) {
 #pragma unroll
-        for (uint32_t u = 0; u < kUnroll; ++u) {
-            W[u][0] = load16(wrow + k + u * kKStep);
-            W[u][1] = load16(wrow + k + u * kKStep + 32u);
+        for (uint32_t i = 0; i < XR / 2; ++i)
+            X[i] = *reinterpret_cast<const u32x4v *>(
+                m.x + static_cast<uint64_t>(umin(2u * i + half, a.tokens - 1u)) * m.cols + at);
+    };
+    auto put_w = [&](uint32_t i) {
+        const uint32_t r = 2u * i + half;
+        wl[r * 32u + ((pl + r) & 31u)] = W[i];
+    };
+    auto put_x = [&]() {
+#pragma unroll
+        for (uint32_t i = 0; i < XR / 2; ++i)
+            *reinterpret_cast<u32x4v *>(xl + (2u * i + half) * kRowsXStride + 16u * pl) = X[i];
+    };
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    auto products = [&](uint32_t u) {
+        const uint8_t *row = xl + (j & (XR - 1u)) * kRowsXStride + 2u * (kKStep * u + 8u * g);
+        const uint4 x0 = *reinterpret_cast<const uint4 *>(row);
+        const uint4 x1 = *reinterpret_cast<const uint4 *>(row + 64u);
+        const u32x4v w0 = wl[j * 32u + ((8u * u + g + j) & 31u)];
+        const u32x4v w1 = wl[j * 32u + ((8u * u + 4u + g + j) & 31u)];
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(x0), __builtin_bit_cast(bf16x8, w0), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(x1), __builtin_bit_cast(bf16x8, w1), acc, 0, 0, 0);
+    };
+    uint32_t k0 = wave * m.kchunk, k = k0;
+    if (k < m.cols) {
+        uint32_t k1 = umin(m.cols, k0 + m.kchunk);
+        {
+            const uint32_t at = piece(k, k1);
+            load_x(at);
+#pragma unroll
+            for (uint32_t i = 0; i < 8; ++i) load_w(i, at);
         }
+        for (;;) {
+            // the slab after this one: in the range, or the wave's next range
+            const bool turn = k + kKPerIter >= k1;
+            const uint32_t n0 = turn ? k0 + kWaves * m.kchunk : k0;
+            const uint32_t kn = turn ? n0 : k + kKPerIter;
+            if (kn >= m.cols) break;
+            const uint32_t n1 = umin(m.cols, n0 + m.kchunk);
+            const uint32_t at = piece(kn, n1);
+            // each register takes the next slab's load as soon as it is in
+            // LDS, so a slab of weights stays in flight
+            put_x();
+            __builtin_amdgcn_sched_barrier(0);
+            load_x(at);
 #pragma unroll
-        for (uint32_t u = 0; u < kUnroll; ++u) step(k + u * kKStep, W[u][0], W[u][1]);
+            for (uint32_t i = 0; i < 8; ++i) {
+                put_w(i);
+                __builtin_amdgcn_sched_barrier(0);
+                load_w(i, at);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const uint32_t steps = umin(kUnroll, (k1 - k) / kKStep);  // uniform
+#pragma unroll
+            for (uint32_t u = 0; u < kUnroll; ++u)
+                if (u < steps) products(u);
+            if (turn) {
+                total += acc;
+                acc = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+            k = kn;
+            k0 = n0;
+            k1 = n1;
+        }
+        const uint32_t steps = umin(kUnroll, (k1 - k) / kKStep);
+        put_x();
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i) put_w(i);
+#pragma unroll
+        for (uint32_t u = 0; u < kUnroll; ++u)
+            if (u < steps) products(u);
+        total += acc;
     }
-    for (; k < k1; k += kKStep) step(k, load16(wrow + k), load16(wrow + k + 32u));
-    write_tile<1>(a, m, rb, s, j, g, acc);
+    __syncthreads();  // the totals reuse the slabs
+    f32x4 *totals = reinterpret_cast<f32x4 *>(lds);
+    totals[tid] = total;
+    __syncthreads();
+    if (wave == 0u) {
+        f32x4 sum[1] = {((totals[lane] + totals[64u + lane]) + totals[128u + lane]) + totals[192u + lane]};
+        write_tile<1>(a, m, rb, 0, j, g, sum);
+    }
 }
 
-// Four or more tokens: a workgroup of kSlabWaves waves covers 16*kSlabWaves features
+// From 17 tokens: a workgroup of kSlabWaves waves covers 16*kSlabWaves features
 // over one k range and stages the activations of each 256-k slab in LDS once
 // for all its waves (rows padded by 16 bytes so the 16 lanes of one read
 // pass hit distinct banks).
@@ -390,6 +486,13 @@ void split_into(uint32_t cols, uint32_t ks_req, uint32_t *ksplit, uint32_t *kchu
     *ksplit = (cols + kc - 1) / kc;  // no empty range
 }
 
+// k range of the rows kernel: 1024 columns, or a quarter of a row shorter than
+// four of them (in whole slabs), so that every wave has one.
+uint32_t rows_range(uint32_t cols) {
+    const uint32_t quarter = (cols + kWaves * kKPerIter - 1) / (kWaves * kKPerIter) * kKPerIter;
+    return quarter < kKTargetFew ? quarter : kKTargetFew;
+}
+
 uint32_t base_ranges(uint32_t cols, uint32_t tokens) {
     const uint32_t target = tokens <= kFewTokens ? kKTargetFew : kKTargetMany;
     const uint32_t ks = (cols + target - 1) / target;
@@ -437,7 +540,6 @@ constexpr size_t kMaxSplits = 64;
 
 int choose_ranges(const df11_matrix *mats, uint32_t n_mats, uint32_t tokens, uint32_t *ks_req) {
     for (uint32_t m = 0; m < n_mats; ++m) ks_req[m] = base_ranges(mats[m].cols, tokens);
-    if (tokens <= kFewTokens) return DF11_OK;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return DF11_E_HIP;
     std::lock_guard<std::mutex> lk(g_split_mu);
@@ -533,9 +635,9 @@ int plan(const uint16_t *weights, uint64_t n_weights, const df11_matrix *mats, u
             (reinterpret_cast<uintptr_t>(y[m]) & 3u))
             return DF11_E_INVALID_ARG;
     }
-    uint32_t ks_req[kMax];
-    rc = choose_ranges(mats, n_mats, tokens, ks_req);
-    if (rc) return rc;
+    const bool few = tokens <= kRowsTokens;
+    uint32_t ks_req[kMax] = {};
+    if (!few && (rc = choose_ranges(mats, n_mats, tokens, ks_req)) != DF11_OK) return rc;
 
     GemmArgs g{};
     ReduceArgs r{};
@@ -544,36 +646,46 @@ int plan(const uint16_t *weights, uint64_t n_weights, const df11_matrix *mats, u
     r.part = static_cast<const float *>(workspace);
     g.n_mats = r.n_mats = n_mats;
     g.tokens = r.tokens = tokens;
-    uint64_t tiles = 0, wgs = 0, part = 0, outs = 0;
-    for (uint32_t m = 0; m < n_mats; ++m) {
+    uint64_t wgs = 0, part = 0, outs = 0;
+    uint32_t order[kMax];  // the matrices as they are launched
+    for (uint32_t m = 0; m < n_mats; ++m) order[m] = m;
+    // a workgroup of the rows kernel takes as long as its row is: the longest
+    // first, so that the launch does not end on them
+    if (few)
+        std::stable_sort(order, order + n_mats,
+                         [&](uint32_t p, uint32_t q) { return mats[p].cols > mats[q].cols; });
+    for (uint32_t i = 0; i < n_mats; ++i) {
+        const uint32_t m = order[i];
         const df11_matrix &d = mats[m];
         uint32_t ks, kc;
-        split_into(d.cols, ks_req[m], &ks, &kc);
-        g.tile_start[m] = static_cast<uint32_t>(tiles);
-        g.wg_start[m] = static_cast<uint32_t>(wgs);
-        g.ksplit[m] = r.ksplit[m] = ks;
-        g.kchunk[m] = kc;
-        g.rows[m] = r.rows[m] = d.rows;
-        g.cols[m] = d.cols;
-        g.w_off[m] = d.offset;
-        g.part_off[m] = r.part_off[m] = part;
-        g.x[m] = x[m];
-        g.y[m] = r.y[m] = y[m];
-        r.out_start[m] = static_cast<uint32_t>(outs);
-        tiles += static_cast<uint64_t>(d.rows / kTileRows) * ks;
-        wgs += static_cast<uint64_t>((d.rows + kTileRows * kSlabWaves - 1) / (kTileRows * kSlabWaves)) * ks;
+        if (few) {
+            ks = 1;
+            kc = rows_range(d.cols);
+        } else {
+            split_into(d.cols, ks_req[m], &ks, &kc);
+        }
+        g.wg_start[i] = static_cast<uint32_t>(wgs);
+        g.ksplit[i] = r.ksplit[i] = ks;
+        g.kchunk[i] = kc;
+        g.rows[i] = r.rows[i] = d.rows;
+        g.cols[i] = d.cols;
+        g.w_off[i] = d.offset;
+        g.part_off[i] = r.part_off[i] = part;
+        g.x[i] = x[m];
+        g.y[i] = r.y[i] = y[m];
+        r.out_start[i] = static_cast<uint32_t>(outs);
+        wgs += few ? static_cast<uint64_t>(d.rows / kTileRows)
+                   : static_cast<uint64_t>((d.rows + kTileRows * kSlabWaves - 1) / (kTileRows * kSlabWaves)) * ks;
         if (ks > 1) {
             part += static_cast<uint64_t>(d.rows) * ks * tokens;
             outs += static_cast<uint64_t>(d.rows) * tokens;
         }
-        if (tiles > 0xFFFFFFFFull || outs > 0xFFFFFFFFull) return DF11_E_UNSUPPORTED;
+        if (wgs > 0xFFFFFFFFull || outs > 0xFFFFFFFFull) return DF11_E_UNSUPPORTED;
     }
     for (uint32_t m = n_mats; m <= kMax; ++m) {
-        g.tile_start[m] = static_cast<uint32_t>(tiles);
         g.wg_start[m] = static_cast<uint32_t>(wgs);
         r.out_start[m] = static_cast<uint32_t>(outs);
     }
-    g.num_tiles = static_cast<uint32_t>(tiles);
     g.num_wg = static_cast<uint32_t>(wgs);
     r.total = static_cast<uint32_t>(outs);
     *gp = g;
@@ -584,13 +696,13 @@ int plan(const uint16_t *weights, uint64_t n_weights, const df11_matrix *mats, u
 int launch(const GemmArgs &g, const ReduceArgs &r, hipStream_t stream) {
     const uint32_t mt = (g.tokens + 15) / 16;
     const dim3 block(64 * kWaves), slab_block(64 * kSlabWaves);
-    const dim3 grid_tiles((g.num_tiles + kWaves - 1) / kWaves), grid_wg(g.num_wg);
+    const dim3 grid_wg(g.num_wg);
     switch (mt) {
     case 1:
-        if (g.tokens < kSlabMinTokens)
-            hipLaunchKernelGGL(gemm_tiles_kernel, grid_tiles, block, 0, stream, g);
+        if (g.tokens <= 8)
+            hipLaunchKernelGGL(gemm_rows_kernel<8>, grid_wg, block, 0, stream, g);
         else
-            hipLaunchKernelGGL(gemm_slab_kernel<1>, grid_wg, slab_block, 0, stream, g);
+            hipLaunchKernelGGL(gemm_rows_kernel<16>, grid_wg, block, 0, stream, g);
         break;
     case 2: hipLaunchKernelGGL(gemm_slab_kernel<2>, grid_wg, slab_block, 0, stream, g); break;
     case 3: hipLaunchKernelGGL(gemm_slab_kernel<3>, grid_wg, slab_block, 0, stream, g); break;

@@ -159,3 +159,17 @@ def test_random_blocks_forward(seed):
     for p, q in zip(y_dec, y_raw):
         assert np.array_equal(p.view(np.uint32), q.view(np.uint32)), f"shapes {shapes} t={tokens}"
     check_against_oracle(w, mats, xs, y_dec)
+
+
+@pytest.mark.parametrize("tokens", [1, 8, 9, 16, 17])
+@pytest.mark.parametrize("cols", [64, 192, 256, 320, 1088, 4096, 4224, 8256])
+def test_whole_rows_in_one_workgroup(tokens, cols):
+    """Up to 16 tokens a workgroup's four waves share a row's k ranges: rows
+    shorter than a wave's range, ranges that end inside a slab, waves with no,
+    one and several ranges; matrices of other widths before and after, so that
+    the launch order differs from the caller's."""
+    w, mats = make_block([(32, 512), (16, cols), (48, 2048)], tokens + cols)
+    xs = [synth.activations(tokens, c, 71, i, tokens) for i, (_, _, c) in enumerate(mats)]
+    import torch
+    check_against_oracle(w, mats, xs, run_gemm(
+        torch.from_numpy(w.view(np.int16)).cuda().view(torch.bfloat16), mats, xs))
