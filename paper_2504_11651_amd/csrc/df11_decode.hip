@@ -337,7 +337,9 @@ constexpr uint32_t kWaveChoices[4] = {4, 8, 12, 16};
 //    24.0 M   64  2.59       16.8                  16.9             17.2     16.8      17.5
 //    20.0 M   64  2.85       15.7                  16.1             14.9               15.2
 //    16.8 M   64  2.59       13.1      17.0        13.7             13.0     13.2      12.7
+//   329.3 M  256  2.59      222.6                 206.1            226.3
 //   120.0 M  256  2.59       83.5     102          77.8             83.1               84.4
+//   218.1 M  256  2.64      150.5                                  149.9
 //   120.0 M  256  2.85       84.7     114          84.8             83.1               87.2
 //   120.0 M  512  2.59       86.3     108                           78.6               78.7
 // "hold": a wave waits for its stores before it starts the next block.  With
@@ -367,11 +369,12 @@ WaveRule wave_rule(const df11_stream *s, uint64_t cus) {
         return {3u, false};
     }
     if (z.num_chunks < kLongChunks * cus) return {0u, false};
+    const bool mixed = z.total_bits * 50 > z.n_elems * 131;  // mean above 2.62 bits
     if (T == 128) {
-        const bool mixed = z.total_bits * 50 > z.n_elems * 131;  // mean above 2.62 bits
         const bool three = long_codes || (mixed && z.num_chunks < kVeryLongChunks * cus);
         return {three ? 3u : 2u, three};
     }
+    if (T == 256 && !mixed) return {3u, false};
     return {4u, false};
 }
 

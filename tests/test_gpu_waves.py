@@ -34,7 +34,7 @@ def two_sigmas(n):
     (64, random_bits, 6_900_007, 5), (64, random_bits, 8_000_001, 4),
     (64, random_bits, 25_800_009, 3), (128, gaussian, 80_000_001, 2),
     (128, two_sigmas, 80_000_001, 3), (128, random_bits, 25_800_009, 3),
-    (256, gaussian, 80_000_001, 4)],
+    (256, gaussian, 80_000_001, 3), (256, two_sigmas, 80_000_001, 4)],
     ids=lambda v: getattr(v, "__name__", str(v)))
 def test_waves_per_simd(T, make, n, per_simd):
     import torch
