@@ -280,10 +280,11 @@ class DeviceStream:
         self._st = Stream(self.exp.data_ptr(), self.sm.data_ptr(), self.gaps.data_ptr(),
                           self.block_pos.data_ptr(), self.tables.data_ptr(), self.sizes,
                           self.layout)
+        self._ref = ctypes.byref(self._st)
 
     @property
     def n_elems(self) -> int:
-        return int(self.sizes.n_elems)
+        return self.sizes.n_elems
 
     def struct(self) -> Stream:
         return self._st
@@ -322,11 +323,11 @@ def decode_block(ds: DeviceStream, out=None, stream=None):
     if out.numel() < n or out.element_size() != 2 or not out.is_contiguous():
         raise ValueError("out must be a contiguous 2-byte tensor with n_elems elements")
     _on_device(out, ds.device, "out")
-    if stream is None:
-        stream = torch.cuda.current_stream(ds.device)
-    handle = stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
-    _check(lib().df11_decode_block(ctypes.byref(ds.struct()), ctypes.c_void_p(out.data_ptr()),
-                                   ctypes.c_void_p(handle)), "df11_decode_block")
+    # plain integers: the declared argument types convert them, and a small
+    # stream's decode takes about as long as this call
+    rc = (_lib or lib()).df11_decode_block(ds._ref, out.data_ptr(), _handle(stream, ds.device))
+    if rc:
+        _check(rc, "df11_decode_block")
     return out
 
 
