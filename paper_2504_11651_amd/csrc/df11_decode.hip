@@ -65,11 +65,11 @@ __global__ __launch_bounds__(64 * W) void df11_decode_wave_kernel(DecodeArgs a) 
     ChunkWords cw{};
     if (first_block < a.num_blocks) cw = load_chunk<64>(a, first_block, lane);
     stage_table_blob(a, lds, tid, 64 * W);
-    const Tables tb = stage_tables(a, lds);
     const uint32_t buf_off = a.table_lds_bytes + wave * a.buf_bytes;
     uint8_t *buf = lds + buf_off + kBufLead;
     __syncthreads();
     if (first_block >= a.num_blocks) return;
+    const Tables tb = staged_tables(a, lds);
     Chunk ch[1] = {chunk_setup<64>(a, cw, first_block, lane)};
     Range r = block_range(a, cw);
 
@@ -129,11 +129,11 @@ __global__ __launch_bounds__(64 * W) void df11_decode_pair_kernel(DecodeArgs a) 
     PairWords pw{};
     if (first_block < a.num_blocks) pw = load_pair<128>(a, first_block, 2u * lane);
     stage_table_blob(a, lds, tid, 64 * W);
-    const Tables tb = stage_tables(a, lds);
     const uint32_t buf_off = a.table_lds_bytes + wave * a.buf_bytes;
     uint8_t *buf = lds + buf_off + kBufLead;
     __syncthreads();
     if (first_block >= a.num_blocks) return;
+    const Tables tb = staged_tables(a, lds);
     Chunk ch[2];
     pair_setup<128>(a, pw, first_block, 2u * lane, ch);
     Range r = block_range(a, pw.bp0, pw.bp1);
@@ -192,11 +192,11 @@ __global__ __launch_bounds__(T / 2) void df11_decode_block_pair_kernel(DecodeArg
     PairWords pw{};
     if (blockIdx.x < a.num_blocks) pw = load_pair<T>(a, blockIdx.x, 2u * tid);
     stage_table_blob(a, lds, tid, NT);
-    const Tables tb = stage_tables(a, lds);
     uint32_t *wave_sums = reinterpret_cast<uint32_t *>(lds + a.table_lds_bytes);
     const uint32_t buf0 = a.table_lds_bytes + 4 * kScanSlots;
     __syncthreads();
     if (blockIdx.x >= a.num_blocks) return;
+    const Tables tb = staged_tables(a, lds);
     Chunk ch[2];
     pair_setup<T>(a, pw, blockIdx.x, 2u * tid, ch);
     Range r = block_range(a, pw.bp0, pw.bp1);
@@ -251,13 +251,14 @@ __global__ __launch_bounds__(T) void df11_decode_block_kernel(DecodeArgs a) {
     const uint32_t lane = tid & 63u;
     const uint32_t wave = tid >> 6;
     stage_table_blob(a, lds, tid, T);
-    const Tables tb = stage_tables(a, lds);
     uint32_t *wave_sums = reinterpret_cast<uint32_t *>(lds + a.table_lds_bytes);
     const uint32_t buf_off = a.table_lds_bytes + 4 * kScanSlots;
     uint8_t *buf = lds + buf_off + kBufLead;
 
     if (blockIdx.x >= a.num_blocks) return;
     ChunkWords cw = load_chunk<T>(a, blockIdx.x, tid);
+    __syncthreads();
+    const Tables tb = staged_tables(a, lds);
     Chunk ch[1] = {chunk_setup<T>(a, cw, blockIdx.x, tid)};
     Range r = block_range(a, cw);
 
@@ -270,7 +271,7 @@ __global__ __launch_bounds__(T) void df11_decode_block_kernel(DecodeArgs a) {
         prefetch_sm(a, r, gr, S);
         const uint32_t edge_sm = prefetch_edge_sm(a, r, tid);
 
-        __syncthreads();  // tables staged / previous block's buffer consumed
+        __syncthreads();  // the previous block's buffer is consumed
         for (uint32_t i = tid; i < (a.buf_bytes >> 4); i += T)
             reinterpret_cast<uint4 *>(lds + buf_off)[i] = make_uint4(0u, 0u, 0u, 0u);
 

@@ -100,7 +100,12 @@ struct Tables {
     uint32_t lane_lj, lane_offset, lane_sorted;
 };
 
-__device__ __forceinline__ Tables stage_tables(const DecodeArgs &a, uint8_t *lds) {
+// The tables as a wave uses them, read from LDS: the caller's barrier after
+// stage_table_blob comes first.  From memory the lanes' words are one more
+// round trip before a workgroup's first block; us, from memory and from LDS:
+// 16.8 M weights in 64-chunk blocks 14.97 and 14.43, 4.2 M in 256-chunk
+// blocks 7.90 and 7.61 (12-bit tables 9.00 and 8.68).
+__device__ __forceinline__ Tables staged_tables(const DecodeArgs &a, const uint8_t *lds) {
     Tables tb;
     const uint32_t ent_bytes = 8u << a.lut_bits;
     tb.lj_last = reinterpret_cast<const uint32_t *>(lds + ent_bytes);
@@ -112,12 +117,11 @@ __device__ __forceinline__ Tables stage_tables(const DecodeArgs &a, uint8_t *lds
     asm("" : "+v"(tb.addr_mask));
     tb.lut_bits = a.lut_bits;
     tb.max_len = a.max_len;
-    const uint8_t *blob = a.tables + ent_bytes;
     const uint32_t lane = threadIdx.x & 63u, L = lane < 33u ? lane : 0u;
-    const uint32_t lj = reinterpret_cast<const uint32_t *>(blob)[L];
+    const uint32_t lj = tb.lj_last[L];
     tb.lane_lj = lane > a.lut_bits && lane < a.max_len ? lj : 0xFFFFFFFFu;
-    tb.lane_offset = reinterpret_cast<const uint32_t *>(blob)[33u + L];
-    tb.lane_sorted = rotate_exponents(reinterpret_cast<const uint32_t *>(blob)[66u + lane]);
+    tb.lane_offset = tb.offset[L];
+    tb.lane_sorted = rotate_exponents(reinterpret_cast<const uint32_t *>(tb.sorted)[lane]);
     return tb;
 }
 

@@ -393,8 +393,8 @@ df11_gemv_wave_kernel(GemvArgs g) {
     const uint32_t main_grid = gridDim.x - g.boundary_grid;
     if (blockIdx.x < g.boundary_grid) {
         stage_table_blob(a, lds, tid, 64 * W);
-        const Tables tb = stage_tables(a, lds);
         __syncthreads();
+        const Tables tb = staged_tables(a, lds);
         const uint32_t q = blockIdx.x * W + wave;
         if (q < 2u * g.n_mats)
             boundary_block(g, tb, lds, a.table_lds_bytes + g.x_bytes + wave * a.buf_bytes, lane, q);
@@ -407,11 +407,11 @@ df11_gemv_wave_kernel(GemvArgs g) {
     if (first_group + wave < a.num_blocks) cw = load_chunk<64>(a, first_group + wave, lane);
     if (first_group < a.num_blocks) group_pos = block_positions(a)[first_group];
     stage_table_blob(a, lds, tid, 64 * W);
-    const Tables tb = stage_tables(a, lds);
     uint8_t *xs = lds + a.table_lds_bytes;
     const uint32_t buf_off = a.table_lds_bytes + g.x_bytes + wave * a.buf_bytes;
     uint8_t *buf = lds + buf_off + kBufLead;
     __syncthreads();
+    const Tables tb = staged_tables(a, lds);
     Chunk ch[1] = {chunk_setup<64>(a, cw, first_group + wave, lane)};
     Range r = block_range(a, cw);
     Current cur{};
