@@ -39,6 +39,7 @@
 // Integer work only; no MFMA.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <mutex>
 #include <vector>
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(T) void df11_decode_block_kernel(DecodeArgs a) {
 using KernelFn = void (*)(DecodeArgs);
 
 struct LaunchShape {
-    uint32_t threads, lut_bits, buf;  // key
+    uint32_t threads, lut_bits, buf, most, large;  // key
     KernelFn fn;
     uint32_t block, lds, per_cu, waves_per_group, twin_bufs;
 };
@@ -349,8 +350,9 @@ constexpr uint32_t kWaveChoices[4] = {4, 8, 12, 16};
 // A stream of few blocks per wave takes more waves instead: its last round
 // and the latency of each round dominate.
 struct WaveRule {
-    uint32_t per_simd;  // 0: every wave that fits
+    uint32_t per_simd;   // 0: every wave that fits
     bool hold;
+    bool large = false;  // T <= 128: among equal counts the largest workgroups
 };
 
 // Chunks per CU up to which a T = 64 stream takes 5 waves (2.65 rounds of
@@ -365,6 +367,10 @@ WaveRule wave_rule(const df11_stream *s, uint64_t cus) {
     const uint32_t T = s->layout.threads_per_block;
     const bool long_codes = z.total_bits > z.n_elems * 11 / 4;  // mean above 2.75 bits
     if (T == 64) {
+        // 33 KB of tables per workgroup: a short stream takes few, large ones
+        // (us, before, 4-wave and 12-wave workgroups: 4.2 M weights 7.4, 8.2,
+        // 6.5; 16.8 M 15.9, 16.5, 15.1; 24 M 19.2, 20.4, 17.8)
+        if (s->layout.lut_bits == 12 && z.num_chunks <= kFourWaves * cus) return {0u, false, true};
         if (z.num_chunks <= kFiveWaves * cus) return {5u, false};
         if (z.num_chunks <= (long_codes ? kLongChunks : kFourWaves) * cus) return {4u, true};
         return {3u, false};
@@ -426,6 +432,7 @@ int fit(DeviceInfo &di, int slot, KernelFn fn, uint32_t threads, uint32_t lds, i
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, reinterpret_cast<const void *>(fn),
                                                      static_cast<int>(threads), lds) != hipSuccess)
         return DF11_E_HIP;
+    *per_cu = std::min(*per_cu, static_cast<int>(lds_fit(static_cast<uint32_t>(di.max_lds), lds)));
     return DF11_OK;
 }
 
@@ -446,14 +453,18 @@ int shape_for(const df11_stream *s, KernelFn *fn, uint32_t *grid, uint32_t *bloc
                 hipSuccess)
             return DF11_E_HIP;
     }
+    const WaveRule rule = wave_rule(s, static_cast<uint64_t>(di.cus));
+    const uint32_t most = 4u * (rule.per_simd ? rule.per_simd : 16u);  // waves per CU; 4 SIMDs
     const LaunchShape *found = nullptr;
     for (const LaunchShape &ls : di.shapes)
-        if (ls.threads == T && ls.lut_bits == K && ls.buf == buf) found = &ls;
+        if (ls.threads == T && ls.lut_bits == K && ls.buf == buf && ls.most == most &&
+            ls.large == rule.large)
+            found = &ls;
     if (!found) {
-        LaunchShape ls{T, K, buf, nullptr, 0, 0, 0, 1, 0};
+        LaunchShape ls{T, K, buf, most, rule.large, nullptr, 0, 0, 0, 1, 0};
         if (T == 64 || T == 128) {
-            // one wave per block: most resident waves per CU; fewer waves per
-            // workgroup on a tie
+            // one wave per block: the workgroup size that comes nearest to the
+            // rule's waves per CU from below; on a tie as the rule says
             int best_waves = 0;
             for (int i = 0; i < 4; ++i) {
                 const uint32_t W = kWaveChoices[i];
@@ -461,8 +472,10 @@ int shape_for(const df11_stream *s, KernelFn *fn, uint32_t *grid, uint32_t *bloc
                 int pc = 0;
                 int rc = fit(di, T == 64 ? i : 4 + i, fn, 64 * W, tab + W * buf, &pc);
                 if (rc) return rc;
-                if (pc * static_cast<int>(W) > best_waves) {
-                    best_waves = pc * static_cast<int>(W);
+                pc = std::min(pc, static_cast<int>(most / W));
+                const int waves = pc * static_cast<int>(W);
+                if (waves > best_waves || (rule.large && waves > 0 && waves == best_waves)) {
+                    best_waves = waves;
                     ls.fn = fn;
                     ls.block = 64 * W;
                     ls.lds = tab + W * buf;
@@ -497,6 +510,8 @@ int shape_for(const df11_stream *s, KernelFn *fn, uint32_t *grid, uint32_t *bloc
             if (pc < 1) return DF11_E_UNSUPPORTED;
             ls.per_cu = static_cast<uint32_t>(pc);
         }
+        // (a workgroup of T >= 256 is a block: at least one, whatever the rule)
+        ls.per_cu = std::min(ls.per_cu, std::max(most * 64u / ls.block, 1u));
         if (di.shapes.size() >= kMaxShapes) di.shapes.erase(di.shapes.begin());  // oldest goes
         di.shapes.push_back(ls);
         found = &di.shapes.back();
@@ -508,12 +523,8 @@ int shape_for(const df11_stream *s, KernelFn *fn, uint32_t *grid, uint32_t *bloc
     const uint64_t W = found->waves_per_group;
     const uint64_t nb = s->sizes.num_blocks;
     const uint64_t blocks_needed = (nb + W - 1) / W;
-    uint64_t per_cu = found->per_cu;
-    const WaveRule rule = wave_rule(s, static_cast<uint64_t>(di.cus));
-    const uint64_t cap = rule.per_simd * 4ull * 64 / found->block;  // workgroups; 4 SIMDs per CU
-    if (cap >= 1 && per_cu > cap) per_cu = cap;
     *hold = rule.hold;
-    uint64_t g = static_cast<uint64_t>(di.cus) * per_cu;
+    uint64_t g = static_cast<uint64_t>(di.cus) * found->per_cu;
     if (g > blocks_needed) g = blocks_needed;
     *grid = static_cast<uint32_t>(g ? g : 1);
     return DF11_OK;

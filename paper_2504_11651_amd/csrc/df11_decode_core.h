@@ -706,6 +706,14 @@ inline bool layout_supported(uint32_t T) {
     return T == 64 || T == 128 || T == 256 || T == 512 || T == 1024;
 }
 
+// Workgroups of `lds` bytes that a CU's LDS holds at once.  gfx950 hands LDS
+// out in pieces of 1280 bytes; the occupancy query counts plain bytes, and a
+// persistent grid one workgroup per CU too large runs in two unequal turns.
+inline uint32_t lds_fit(uint32_t cu_lds, uint32_t lds) {
+    constexpr uint32_t kPiece = 1280;
+    return lds ? cu_lds / ((lds + kPiece - 1) / kPiece * kPiece) : ~0u >> 1;
+}
+
 inline uint32_t buf_bytes_for(uint32_t max_elems) {
     return (max_elems + kBufSlack + 15u) & ~15u;
 }
