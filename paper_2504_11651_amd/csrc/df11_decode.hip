@@ -319,70 +319,112 @@ constexpr uint32_t kWaveChoices[4] = {4, 8, 12, 16};
 // Waves per SIMD.  A stream's reads and writes are spread over every wave's
 // block, and the more blocks are in flight at once the less of the memory's
 // rate their mix reaches; fewer waves than the registers and LDS allow are
-// faster as soon as they still cover the decode's latency.  Times in us on
-// an MI355X, streams rotating so that none is cached; "before" is the same
-// rule's line when every wave decoded longer and 4 to 6 per SIMD were best.
-//   weights, T, mean code  before   2 waves   3 waves  3, hold   4 waves  4, hold   5 waves
-//   855.6 M  128  2.69      562       519       565      542       595
-//   300.0 M  128  2.59      192.2     176.0     194.1    185.5     204.7
-//   218.1 M  128  2.59      140.1     130.2     142.1    134.3     149.2
-//   218.1 M  128  2.64      140.3     135.4     142.3    134.6     149.8
-//    91.7 M  128  2.64       59.3      60.6      58.7     57.4      61.6
-//   218.1 M  128  2.85      140.7     138.6     142.5    135.1     150.7
-//    80.0 M  128  2.59       52.7      51.2      53.8     51.5      54.4
-//    67.0 M  128  2.59       44.9      46.9      46.2               44.6
-//    16.0 M  128  2.59       14.6      15.7      13.4               13.2
-//   190.0 M   64  2.59      121.5     150         118.5             126.9    118.3     134.3
-//   100.0 M   64  2.85       66.2                  62.3             68.6     63.9      71.7
-//    50.0 M   64  2.85       30.6                  31.3             32.5     29.4      32.7
-//    50.0 M   64  2.59       31.0                  29.2             31.7               32.9
-//    24.0 M   64  2.59       16.8                  16.9             17.2     16.8      17.5
-//    20.0 M   64  2.85       15.7                  16.1             14.9               15.2
-//    16.8 M   64  2.59       13.1      17.0        13.7             13.0     13.2      12.7
-//   329.3 M  256  2.59      222.6                 206.1            226.3
-//   120.0 M  256  2.59       83.5     102          77.8             83.1               84.4
-//   218.1 M  256  2.64      150.5                                  149.9
-//   120.0 M  256  2.85       84.7     114          84.8             83.1               87.2
-//   120.0 M  512  2.59       86.3     108                           78.6               78.7
-// "hold": a wave waits for its stores before it starts the next block.  With
-// longer codes the lookups per weight grow and two waves no longer cover them;
-// a third one that holds does, without as many blocks in flight.
-// A stream of few blocks per wave takes more waves instead: its last round
-// and the latency of each round dominate.
+// faster as long as they still cover the decode's latency.  How many that takes
+// follows from the lookups per weight, that is from the mean code length against
+// the table's index width K.  A stream of few blocks per wave takes more waves:
+// its last round and the latency of each round dominate.
 struct WaveRule {
     uint32_t per_simd;   // 0: every wave that fits
-    bool hold;
-    bool large = false;  // T <= 128: among equal counts the largest workgroups
+    bool hold;           // a wave waits for its stores before its next block
+    bool large = false;  // the largest workgroups of which two fit a CU, among equal counts
 };
 
-// Chunks per CU up to which a T = 64 stream takes 5 waves (2.65 rounds of
-// blocks), then 4 with hold (until 4.6 rounds of them, with long codes until
-// a stream is long), and from which a stream is long (12 rounds of two waves
-// on 128 chunks) or very long.
-constexpr uint64_t kFiveWaves = 3400, kFourWaves = 4725, kLongChunks = 12288,
-                   kVeryLongChunks = 65536;
+// Times in us on an MI355X by graph replay, streams rotating ("all": every
+// wave that fits, 4 to 8; "h": with hold; "before": 4 to 6 per SIMD, when every
+// wave decoded longer).  Codes / K is the mean code length over the index width.
+//   weights   T   K  codes  codes/K  before   2      3      3h     4      4h     5      all
+//   218.1 M  128 11  2.59    0.24     141.4  133.9  141.9  134.9  148.9  147.4
+//   600.0 M  128 11  2.67    0.24     390.9  357.2  392.4  374.1  414.8  403.6
+//   120.0 M  128 11  2.67    0.24      77.5   75.2   80.2   77.0
+//   120.0 M  128 11  2.59    0.24      77.7   75.6   79.0   75.3
+//   218.1 M  128 12  2.67    0.22     142.7  131.4  144.1  136.8  153.4  150.1
+//   218.0 M  128 11  2.17    0.20     136.7  132.6  137.1  134.6  147.5  142.1
+//   218.0 M  128 11  1.63    0.15     140.5  171.0  136.7  141.0  140.6  139.3
+//   218.1 M  128 11  2.85    0.26     140.2  138.8  142.3  135.6  151.0  146.4
+//    80.0 M  128 11  2.85    0.26      55.4   55.7   55.5   53.1   57.4   57.2
+//   218.1 M  128 10  2.59    0.26     141.8  145.8  141.4  134.6  149.0  146.0
+//   218.0 M  128 11  3.24    0.29     143.1  149.0  143.6  135.6  155.2  146.0
+//   218.0 M  128 11  3.53    0.32     147.0  161.1  141.4  140.2  157.5  145.9
+//   100.0 M  128 11  3.53    0.32      67.3   75.5   64.9   67.8   70.5   64.6
+//   218.1 M  128  9  2.67    0.30     151.6  202.3  156.3  166.4  152.0  148.6
+//   218.1 M  128  8  2.59    0.32     165.1  205.0  156.0  166.1  151.4  149.0
+//   218.0 M  128 11  4.53    0.41     184.4  225.8  172.7  192.3  160.4  168.7
+//   218.0 M  128 11  8.00    0.73     242.5  326.1  242.1  263.6  211.1  226.1
+//   130.0 M  128 11  1.63    0.15      88.1  105.1   85.1   89.6   85.4   85.7
+//    20.0 M   64 11  2.59    0.24      17.8          17.1          16.9   17.5   16.6   17.0
+//    28.0 M   64 11  2.85    0.26      22.6          21.6          21.6   22.2   21.4   22.1
+//    32.0 M   64 11  2.59    0.24      24.4          24.0          24.1   24.6   23.5   24.1
+//    36.0 M   64 11  2.67    0.24      26.7          25.7          26.0   26.4   26.2   26.7
+//    36.0 M   64 11  2.85    0.26      27.5          25.2          26.7   26.1   26.9   28.2
+//    60.0 M   64 11  2.85    0.26      41.4          39.3          42.1   39.4   43.4   44.1
+//   190.0 M   64 11  2.59    0.24     122.4  138.0  120.0  122.1  128.6  118.9  135.5  137.6
+//   190.0 M   64 11  2.85    0.26     124.3  147.8  116.4  128.6  129.6  117.9  137.0  139.8
+//   190.0 M   64  9  2.59    0.29     129.5  164.2  124.7  141.4  129.8  122.7  133.9  139.4
+//    28.0 M   64  9  2.67    0.30      23.2          23.6          21.8   23.2   21.5   21.5
+//    32.0 M   64  9  2.67    0.30      25.0          29.4          26.0   27.6   26.0   24.7
+//    36.0 M   64  9  2.67    0.30      28.3          28.1          26.0   28.2   26.8   26.5
+//    28.0 M   64 12  2.59    0.22      21.6          22.5          21.5   23.3          21.8
+//    36.0 M   64 12  2.59    0.22      26.9          26.9          27.4   27.3          28.1
+//    60.0 M   64 12  2.59    0.22      42.5          40.8          41.9   40.5          45.4
+//   100.0 M   64 11  3.24    0.29      71.3   84.2   67.3   79.0   68.9   66.9   71.9   74.2
+//   100.0 M   64 11  3.53    0.32      75.5   90.2   68.9   83.3   68.5   69.5   71.8   74.8
+//   190.0 M   64  9  2.67    0.30     138.0  195.2  145.1  163.5  132.3  139.5  135.6  142.4
+//   190.0 M   64  8  2.59    0.32     145.2  201.3  150.1  167.5  133.2  140.3  136.1  141.1
+//   100.0 M   64 11  4.53    0.41      94.1  126.1   95.2  109.3   81.1   92.0   78.0   82.3
+//   100.0 M   64 11  8.00    0.73     120.3  192.7  137.6  153.4  113.9  125.8  101.6   97.9
+//   100.0 M   64 11  1.00    0.09      64.5   98.2   76.8   79.8   67.5   69.2          62.4
+//   100.0 M   64 11  1.63    0.15      57.0   66.4   54.2   57.6   55.9   54.9   56.7   57.8
+//   218.1 M  256 11  2.59    0.24     150.5  182.6  139.5         149.4         153.9  153.0
+//   218.1 M  256 11  2.85    0.26     151.8  194.5  145.5         150.4         155.4  153.4
+//   120.0 M  256 11  3.24    0.29      88.6  119.6   89.5          82.9          86.7   86.7
+//   218.1 M  256  9  2.59    0.29     161.7  220.9  165.7         148.5         156.0  154.8
+//   218.1 M  256  9  2.85    0.32     167.0  256.2  189.0         163.3         158.8  161.4
+//   120.0 M  256 11  8.00    0.73     156.4  263.1  190.0         156.9         141.0  130.5
+//   218.1 M  512 11  2.59    0.24     155.0  195.6                138.9                148.5
+//   120.0 M  512 11  3.53    0.32      98.5  136.5                 90.1                 89.0
+//   218.1 M  512  9  2.85    0.32     176.8  273.3                177.7                160.2
+//   120.0 M  512 11  8.00    0.73     163.8  278.6                168.3                145.0
+//   218.1 M 1024 11  2.59    0.24     152.8  170.4                                     147.9
+
+// With 12-bit tables every workgroup copies 33 KB of them: short streams take
+// few, large workgroups (us, before, 4-wave and 12-wave workgroups: 4.2 M
+// weights 7.4, 8.2, 6.5; 16.8 M 15.9, 16.5, 15.1; 24 M of 2.85 bits, 4- and
+// 8-wave ones 20.5, 19.7).
+
+// Chunks per CU up to which a T = 64 stream is short (4.4 rounds of five waves'
+// blocks), with 12-bit tables very short, and from which one of larger blocks
+// is long (12 rounds of two waves on 128 chunks).
+constexpr uint64_t kShortChunks = 5632, kVeryShortChunks = 3400, kLongChunks = 12288;
 
 WaveRule wave_rule(const df11_stream *s, uint64_t cus) {
     const df11_sizes &z = s->sizes;
+    const uint64_t bits = z.total_bits, n = z.n_elems, K = s->layout.lut_bits;
     const uint32_t T = s->layout.threads_per_block;
-    const bool long_codes = z.total_bits > z.n_elems * 11 / 4;  // mean above 2.75 bits
+    const bool is_long = z.num_chunks >= kLongChunks * cus;
+    // lookups per weight: codes / K above a number of thousandths; an index of
+    // 8 or 9 bits also meets more codes that are longer than it
+    const auto above = [&](uint64_t thousandths) { return bits * 1000 > n * K * thousandths; };
+    const bool more = above(K < 10 ? 290 : 330), many = above(400);
     if (T == 64) {
-        // 33 KB of tables per workgroup: a short stream takes few, large ones
-        // (us, before, 4-wave and 12-wave workgroups: 4.2 M weights 7.4, 8.2,
-        // 6.5; 16.8 M 15.9, 16.5, 15.1; 24 M 19.2, 20.4, 17.8)
-        if (s->layout.lut_bits == 12 && z.num_chunks <= kFourWaves * cus) return {0u, false, true};
-        if (z.num_chunks <= kFiveWaves * cus) return {5u, false};
-        if (z.num_chunks <= (long_codes ? kLongChunks : kFourWaves) * cus) return {4u, true};
-        return {3u, false};
+        const bool one = bits * 2 < n * 3;  // nearly one symbol: blocks of up to 4096 weights
+        if (one || many) return {0u, false};
+        const bool is_short = z.num_chunks <= kShortChunks * cus;
+        if (K == 12 && is_short) return {z.num_chunks <= kVeryShortChunks * cus ? 0u : 4u, false, true};
+        if (more) return {is_short ? 0u : 4u, false};
+        return {is_short ? 5u : 3u, false};
     }
-    if (z.num_chunks < kLongChunks * cus) return {0u, false};
-    const bool mixed = z.total_bits * 50 > z.n_elems * 131;  // mean above 2.62 bits
+    if (!is_long || many) return {0u, false};
     if (T == 128) {
-        const bool three = long_codes || (mixed && z.num_chunks < kVeryLongChunks * cus);
-        return {three ? 3u : 2u, three};
+        if (more) return {4u, true};
+        if (bits < n * 2) return {0u, false};
+        // two waves cover the lookups of codes of 2.4 to 2.75 bits; shorter
+        // codes make larger blocks, longer ones more lookups
+        const bool two = K > 10 && bits * 5 > n * 12 && bits * 4 < n * 11;
+        return two ? WaveRule{2u, false} : WaveRule{3u, true};
     }
-    if (T == 256 && !mixed) return {3u, false};
-    return {4u, false};
+    if (T == 256) return {above(275) ? 4u : 3u, false};
+    if (T == 512) return {more ? 0u : 4u, false};
+    return {0u, false};  // T = 1024: 4 per SIMD at most
 }
 
 constexpr size_t kMaxShapes = 64;  // cached launch shapes per device
@@ -474,7 +516,7 @@ int shape_for(const df11_stream *s, KernelFn *fn, uint32_t *grid, uint32_t *bloc
                 if (rc) return rc;
                 pc = std::min(pc, static_cast<int>(most / W));
                 const int waves = pc * static_cast<int>(W);
-                if (waves > best_waves || (rule.large && waves > 0 && waves == best_waves)) {
+                if (waves > best_waves || (rule.large && pc > 1 && waves == best_waves)) {
                     best_waves = waves;
                     ls.fn = fn;
                     ls.block = 64 * W;
