@@ -32,8 +32,11 @@
 #include <vector>
 
 #include "df11.h"
+#include "df11_gemm_ranges.h"
 
 namespace {
+
+using namespace df11gemm;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -42,6 +45,7 @@ constexpr uint32_t kTileRows = 16;   // output features per wave
 constexpr uint32_t kKStep = 64;      // k per inner step: two MFMAs
 constexpr uint32_t kUnroll = 4;      // inner steps whose weight loads are issued together
 constexpr uint32_t kKPerIter = kKStep * kUnroll;
+static_assert(kKPerIter == kSlabCols, "the walk's slabs");
 // k range of one wave of the rows kernel, and of one workgroup from 17 tokens
 // (there the split is chosen to balance the CUs).  The workspace up to 8
 // tokens is still counted in ranges of kKTargetFew, so that a caller's sizes
@@ -50,7 +54,7 @@ constexpr uint32_t kKTargetFew = 1024;
 constexpr uint32_t kKTargetMany = 4096;
 constexpr uint32_t kFewTokens = 8;
 constexpr uint32_t kRowsTokens = 16;  // tokens up to which the rows kernel runs
-constexpr uint32_t kWaves = 4;       // waves per workgroup, up to 16 tokens
+constexpr uint32_t kWaves = kRowsWaves;  // per workgroup, up to 16 tokens
 constexpr uint32_t kSlabWaves = 4;   // waves per workgroup sharing one activation slab
 constexpr uint32_t kMax = DF11_MAX_MATRICES;
 
@@ -62,7 +66,7 @@ struct GemmArgs {
     uint32_t num_wg;
     uint32_t wg_start[kMax + 1];    // prefix sums of workgroups per matrix
     uint32_t ksplit[kMax];          // k ranges per matrix
-    uint32_t kchunk[kMax];          // k per range (multiple of kKPerIter)
+    uint32_t kchunk[kMax];          // k per range (whole slabs where there are several)
     uint32_t rows[kMax];
     uint32_t cols[kMax];
     uint64_t w_off[kMax];           // weights
@@ -232,23 +236,18 @@ __global__ __launch_bounds__(64 * kWaves) void gemm_rows_kernel(GemmArgs a) {
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(x0), __builtin_bit_cast(bf16x8, w0), acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(x1), __builtin_bit_cast(bf16x8, w1), acc, 0, 0, 0);
     };
-    uint32_t k0 = wave * m.kchunk, k = k0;
-    if (k < m.cols) {
-        uint32_t k1 = umin(m.cols, k0 + m.kchunk);
+    Slab sl;
+    if (first_slab(0u, m.cols, m.kchunk, wave, &sl)) {
         {
-            const uint32_t at = piece(k, k1);
+            const uint32_t at = piece(sl.k, sl.k1);
             load_x(at);
 #pragma unroll
             for (uint32_t i = 0; i < 8; ++i) load_w(i, at);
         }
         for (;;) {
-            // the slab after this one: in the range, or the wave's next range
-            const bool turn = k + kKPerIter >= k1;
-            const uint32_t n0 = turn ? k0 + kWaves * m.kchunk : k0;
-            const uint32_t kn = turn ? n0 : k + kKPerIter;
-            if (kn >= m.cols) break;
-            const uint32_t n1 = umin(m.cols, n0 + m.kchunk);
-            const uint32_t at = piece(kn, n1);
+            Slab nx;
+            if (!next_slab(m.cols, m.kchunk, sl, &nx)) break;
+            const uint32_t at = piece(nx.k, nx.k1);
             // each register takes the next slab's load as soon as it is in
             // LDS, so a slab of weights stays in flight
             put_x();
@@ -261,19 +260,17 @@ __global__ __launch_bounds__(64 * kWaves) void gemm_rows_kernel(GemmArgs a) {
                 load_w(i, at);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            const uint32_t steps = umin(kUnroll, (k1 - k) / kKStep);  // uniform
+            const uint32_t steps = umin(kUnroll, (sl.k1 - sl.k) / kKStep);  // uniform
 #pragma unroll
             for (uint32_t u = 0; u < kUnroll; ++u)
                 if (u < steps) products(u);
-            if (turn) {
+            if (last_of_range(sl)) {
                 total += acc;
                 acc = f32x4{0.f, 0.f, 0.f, 0.f};
             }
-            k = kn;
-            k0 = n0;
-            k1 = n1;
+            sl = nx;
         }
-        const uint32_t steps = umin(kUnroll, (k1 - k) / kKStep);
+        const uint32_t steps = umin(kUnroll, (sl.k1 - sl.k) / kKStep);
         put_x();
 #pragma unroll
         for (uint32_t i = 0; i < 8; ++i) put_w(i);
@@ -329,7 +326,7 @@ gemm_slab_kernel(GemmArgs a) {
     const uint32_t rbw = local / m.ksplit;        // 64-feature block
     const uint32_t s = local - rbw * m.ksplit;
     const uint32_t k0 = s * m.kchunk;
-    const uint32_t k1 = umin(m.cols, k0 + m.kchunk);
+    const uint32_t k1 = past(k0, m.kchunk, m.cols);
     const uint32_t rb = rbw * kSlabWaves + wave;       // this wave's 16-feature tile
     const bool active = rb * kTileRows < m.rows;   // uniform
 
@@ -415,7 +412,7 @@ gemm_slab_kernel(GemmArgs a) {
     store_slab(k0);
     __syncthreads();
     uint32_t k = k0;
-    for (; k + kSlabK < k1; k += kSlabK) {
+    for (; k1 - k > kSlabK; k += kSlabK) {
         const uint32_t kn = k + kSlabK;
         load_slab(kn);
         // each weight register takes the next slab's load as soon as it is
@@ -480,23 +477,16 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(ReduceArgs a) {
 // Split of one matrix into about ks_req k ranges, each a whole number of
 // slabs (kKPerIter) except the last.
 void split_into(uint32_t cols, uint32_t ks_req, uint32_t *ksplit, uint32_t *kchunk) {
-    uint32_t kc = (cols + ks_req - 1) / ks_req;
+    uint64_t kc = (uint64_t{cols} + ks_req - 1) / ks_req;
     kc = (kc + kKPerIter - 1) / kKPerIter * kKPerIter;
-    *kchunk = kc;
-    *ksplit = (cols + kc - 1) / kc;  // no empty range
-}
-
-// k range of the rows kernel: 1024 columns, or a quarter of a row shorter than
-// four of them (in whole slabs), so that every wave has one.
-uint32_t rows_range(uint32_t cols) {
-    const uint32_t quarter = (cols + kWaves * kKPerIter - 1) / (kWaves * kKPerIter) * kKPerIter;
-    return quarter < kKTargetFew ? quarter : kKTargetFew;
+    if (kc > cols) kc = cols;  // one range
+    *kchunk = static_cast<uint32_t>(kc);
+    *ksplit = static_cast<uint32_t>((cols + kc - 1) / kc);  // no empty range
 }
 
 uint32_t base_ranges(uint32_t cols, uint32_t tokens) {
     const uint32_t target = tokens <= kFewTokens ? kKTargetFew : kKTargetMany;
-    const uint32_t ks = (cols + target - 1) / target;
-    return ks ? ks : 1u;
+    return cols / target + (cols % target ? 1u : 0u);  // cols > 0
 }
 
 // Estimated bytes moved by the busiest CU for one choice of k ranges per
