@@ -196,9 +196,10 @@ typedef struct {
 
 /* Device workspace bytes df11_block_gemm / df11_block_forward need for these
  * matrices at this many tokens: room for the fp32 partial sums of the
- * matrices whose cols are split into k ranges (0 when none is).  Above 8
- * tokens the split is chosen per device to balance its compute units; the
- * value covers every choice, so it depends only on the shapes.  Host, no
+ * matrices whose cols may be split into k ranges (0 when none may).  The split
+ * is chosen per device by its compute units (up to 16 tokens only long rows of
+ * short matrix lists are split, and the rest of the workspace is not written);
+ * the value covers every choice, so it depends only on the shapes.  Host, no
  * device access. */
 int df11_gemm_workspace_bytes(const df11_matrix *mats, uint32_t n_mats, uint32_t tokens,
                               uint64_t *bytes);

@@ -15,9 +15,9 @@
 //     cover each k once whatever order the unit sums in;
 //   - each wave passes its weights through LDS of its own, so that every load
 //     reads whole cache lines;
-//   - up to 16 tokens a workgroup of 4 waves holds whole rows: the waves take
-//     k ranges of 1024 columns in turn, with the activations in LDS too, and
-//     add their totals in LDS;
+//   - up to 16 tokens a workgroup of 4 waves holds whole rows (parts of long
+//     ones where a list has few): the waves take k ranges of 1024 columns in
+//     turn, with the activations in LDS too, and add their totals in LDS;
 //   - from 17 tokens the 4 waves of a workgroup cover 64 features over one k
 //     range and share each 256-k activation slab in LDS; a matrix is split
 //     into ranges of about 4096 columns, or half that where it evens out the
@@ -46,10 +46,9 @@ constexpr uint32_t kKStep = 64;      // k per inner step: two MFMAs
 constexpr uint32_t kUnroll = 4;      // inner steps whose weight loads are issued together
 constexpr uint32_t kKPerIter = kKStep * kUnroll;
 static_assert(kKPerIter == kSlabCols, "the walk's slabs");
-// k range of one wave of the rows kernel, and of one workgroup from 17 tokens
-// (there the split is chosen to balance the CUs).  The workspace up to 8
-// tokens is still counted in ranges of kKTargetFew, so that a caller's sizes
-// and what is refused stay what they were; nothing is written there.
+// k range of one workgroup from 17 tokens (there the split is chosen to balance
+// the CUs).  The workspace is counted in ranges of kKTargetFew up to 8 tokens,
+// then in halves of kKTargetMany; up to 16 tokens few matrices use theirs.
 constexpr uint32_t kKTargetFew = 1024;
 constexpr uint32_t kKTargetMany = 4096;
 constexpr uint32_t kFewTokens = 8;
@@ -156,10 +155,11 @@ __device__ __forceinline__ void write_tile(const GemmArgs &a, const Mat &m, uint
 // half h gives lane group g the 8 values kk + 32h + 8g .. +7, so the four
 // lanes of one row read 64 contiguous bytes per load.
 
-// Up to 16 tokens: one workgroup per 16 features and all of k.  Wave w takes
-// the k ranges w, w + 4, ... one after the other, each summed from zero (as
-// long a chain of roundings as a range, whatever the matrix) and added to the
-// wave's total; the four totals meet in LDS, in wave order.  No partial sums go
+// Up to 16 tokens: one workgroup per 16 features and all of k (a range of it for
+// long rows of lists with few of them).  Wave w takes the workgroup's k ranges
+// w, w + 4, ... one after the other, each summed from zero (as long a chain of
+// roundings as a range, whatever the matrix) and added to the wave's total; the
+// four totals meet in LDS, in wave order.  With whole rows no partial sums go
 // through memory and no second kernel adds them.  A token's row of the matrix
 // unit depends on that token's activations alone, so rows past the last token
 // repeat it and are not written.
@@ -191,10 +191,19 @@ __global__ __launch_bounds__(64 * kWaves) void gemm_rows_kernel(GemmArgs a) {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     uint32_t first;
     const Mat m = select_matrix(a, a.wg_start, blockIdx.x, &first);
-    const uint32_t rb = blockIdx.x - first;
+    const uint32_t local = blockIdx.x - first;
+    uint32_t rb = local, s = 0;
+    if (m.ksplit > 1u) {  // (a division; uniform, and mostly not needed)
+        rb = local / m.ksplit;
+        s = local - rb * m.ksplit;
+    }
+    // the workgroup's columns, counted from the first of them on
+    const uint32_t begin = s * m.kchunk, end = umin(m.kchunk, m.cols - begin);
+    const uint32_t range = rows_range(m.kchunk);
     const uint32_t j = lane & 15u;   // feature row (B) / token row (A)
     const uint32_t g = lane >> 4;    // k group
-    const uint16_t *w = a.w + m.w_off + static_cast<uint64_t>(rb * kTileRows) * m.cols;
+    const uint16_t *w = a.w + m.w_off + static_cast<uint64_t>(rb * kTileRows) * m.cols + begin;
+    const uint16_t *x = m.x + begin;
     f32x4 total = {0.f, 0.f, 0.f, 0.f};
 
     const uint32_t half = lane >> 5, pl = lane & 31u;
@@ -215,7 +224,7 @@ __global__ __launch_bounds__(64 * kWaves) void gemm_rows_kernel(GemmArgs a) {
 #pragma unroll
         for (uint32_t i = 0; i < XR / 2; ++i)
             X[i] = *reinterpret_cast<const u32x4v *>(
-                m.x + static_cast<uint64_t>(umin(2u * i + half, a.tokens - 1u)) * m.cols + at);
+                x + static_cast<uint64_t>(umin(2u * i + half, a.tokens - 1u)) * m.cols + at);
     };
     auto put_w = [&](uint32_t i) {
         const uint32_t r = 2u * i + half;
@@ -237,7 +246,7 @@ __global__ __launch_bounds__(64 * kWaves) void gemm_rows_kernel(GemmArgs a) {
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(x1), __builtin_bit_cast(bf16x8, w1), acc, 0, 0, 0);
     };
     Slab sl;
-    if (first_slab(0u, m.cols, m.kchunk, wave, &sl)) {
+    if (first_slab(end, range, wave, &sl)) {
         {
             const uint32_t at = piece(sl.k, sl.k1);
             load_x(at);
@@ -246,7 +255,7 @@ __global__ __launch_bounds__(64 * kWaves) void gemm_rows_kernel(GemmArgs a) {
         }
         for (;;) {
             Slab nx;
-            if (!next_slab(m.cols, m.kchunk, sl, &nx)) break;
+            if (!next_slab(end, range, sl, &nx)) break;
             const uint32_t at = piece(nx.k, nx.k1);
             // each register takes the next slab's load as soon as it is in
             // LDS, so a slab of weights stays in flight
@@ -264,7 +273,10 @@ __global__ __launch_bounds__(64 * kWaves) void gemm_rows_kernel(GemmArgs a) {
 #pragma unroll
             for (uint32_t u = 0; u < kUnroll; ++u)
                 if (u < steps) products(u);
-            if (last_of_range(sl)) {
+            if (__builtin_expect(last_of_range(sl), 0)) {
+                // (kept a branch: selected, the sums would wait for the matrix
+                // unit after every slab)
+                asm volatile("");
                 total += acc;
                 acc = f32x4{0.f, 0.f, 0.f, 0.f};
             }
@@ -285,7 +297,7 @@ __global__ __launch_bounds__(64 * kWaves) void gemm_rows_kernel(GemmArgs a) {
     __syncthreads();
     if (wave == 0u) {
         f32x4 sum[1] = {((totals[lane] + totals[64u + lane]) + totals[128u + lane]) + totals[192u + lane]};
-        write_tile<1>(a, m, rb, 0, j, g, sum);
+        write_tile<1>(a, m, rb, s, j, g, sum);
     }
 }
 
@@ -489,6 +501,12 @@ uint32_t base_ranges(uint32_t cols, uint32_t tokens) {
     return cols / target + (cols % target ? 1u : 0u);  // cols > 0
 }
 
+// Most k ranges a matrix is split into: what its workspace holds.
+uint32_t most_ranges(uint32_t cols, uint32_t tokens) {
+    const uint32_t base = base_ranges(cols, tokens);
+    return tokens <= kFewTokens ? base : 2 * base;
+}
+
 // Estimated bytes moved by the busiest CU for one choice of k ranges per
 // matrix: workgroup i runs on CU i mod cus (with many tokens every
 // workgroup of the launch is resident at once), moving its weights and,
@@ -580,6 +598,73 @@ int choose_ranges(const df11_matrix *mats, uint32_t n_mats, uint32_t tokens, uin
     return DF11_OK;
 }
 
+// Up to 16 tokens a workgroup holds whole rows, and takes as long as they are
+// however few the workgroups: a wave has one slab after the other, about 0.6 us
+// each.  As long as all the workgroups find a CU of their own, rows are split
+// (into at least 2048 columns) if that saves more slabs in turn than writing,
+// reading and adding the partial sums costs.  Us, a split at every size up to
+// 8 tokens and from 9 in about 4096 columns (before), whole rows, and 2, 4 and 8
+// ranges; * is what the rule takes:
+//                 tokens  before  whole      2      4      8
+//   1024 x  8192     1     12.4    8.5*    9.1    8.9    9.5
+//   1024 x  8192    16     13.4   11.0*   11.0   10.3   10.3
+//    512 x 14336    16     13.6   17.9    13.8   11.0   10.9*
+//   1024 x 14336     1     14.6   13.8    11.7   10.7*  11.7
+//   1024 x 14336    16     14.7   18.6    14.5   12.7*  13.5
+//   2048 x 11008     9     15.9   15.2*   16.4
+//   2048 x 14336    16     17.5   20.1    16.9*  17.6   19.5
+//   3072 x 14336    16     21.4   22.0*   25.2   22.8   25.3
+//    128 x 16384     9     12.2   13.8    11.4    9.4    8.8*
+//   1024 x 28672     1     22.9   22.6    17.8   15.0*  16.0
+//   1024 x 28672    16     20.7   34.2    23.3   17.6*  19.0
+//   2048 x 28672    16     27.8   37.1    27.4*  28.3   29.3
+//   4096 x 28672    16     50.0   44.8*   49.4   48.7   49.9
+// In a list every matrix gets ranges of the longest rows' length: 512 x 14336 and
+// twice 512 x 4096, 16 tokens, 14.7 before, 18.3 whole, 12.0 now.
+constexpr uint32_t kRangeLeast = 2048, kSplitCost = 7;
+
+// Slabs one after the other in a wave of a workgroup that holds `cols` columns.
+uint32_t slabs_in_turn(uint32_t cols) {
+    const uint64_t all = uint64_t{kWaves} * rows_range(cols);
+    return static_cast<uint32_t>((cols + all - 1) / all) * (rows_range(cols) / kSlabCols);
+}
+
+int split_rows(const df11_matrix *mats, uint32_t n_mats, uint32_t tokens, uint32_t *ks_req) {
+    uint32_t longest = 0;
+    for (uint32_t m = 0; m < n_mats; ++m) {
+        ks_req[m] = least_ranges(mats[m].cols);
+        longest = std::max(longest, mats[m].cols);
+    }
+    if (longest < 2 * kRangeLeast) return DF11_OK;
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus <= 0)
+        return DF11_E_HIP;
+    // a range of the longest rows, and as many of the others as come near it
+    uint32_t best = slabs_in_turn(longest);
+    for (uint32_t r = 2; r <= static_cast<uint32_t>(cus); ++r) {
+        uint32_t ks, kc, trial[kMax], turn = 0;
+        split_into(longest, r, &ks, &kc);
+        if (kc < kRangeLeast) break;
+        uint64_t total = 0;
+        for (uint32_t m = 0; m < n_mats; ++m) {
+            trial[m] = std::clamp((mats[m].cols - 1) / kc + 1, least_ranges(mats[m].cols),
+                                  most_ranges(mats[m].cols, tokens));
+            uint32_t part, len;
+            split_into(mats[m].cols, trial[m], &part, &len);
+            total += uint64_t{mats[m].rows / kTileRows} * part;
+            turn = std::max(turn, slabs_in_turn(len));
+        }
+        if (total > static_cast<uint64_t>(cus)) break;
+        if (turn + kSplitCost < best) {
+            best = turn + kSplitCost;
+            std::copy(trial, trial + n_mats, ks_req);
+        }
+    }
+    return DF11_OK;
+}
+
 int check_mats(const df11_matrix *mats, uint32_t n_mats, uint32_t tokens) {
     if (!mats || n_mats == 0 || n_mats > kMax) return DF11_E_INVALID_ARG;
     if (tokens == 0 || tokens > DF11_MAX_TOKENS) return DF11_E_UNSUPPORTED;
@@ -591,14 +676,13 @@ int check_mats(const df11_matrix *mats, uint32_t n_mats, uint32_t tokens) {
     return DF11_OK;
 }
 
-// Partial-sum floats any device's choice of k ranges needs (with many
-// tokens, the most the choice between 1x and 2x the base ranges can take).
+// Partial-sum floats any device's choice of k ranges needs: ranges of about
+// 1024 columns up to 8 tokens, from 9 twice as many as ranges of 4096.
 uint64_t workspace_floats(const df11_matrix *mats, uint32_t n_mats, uint32_t tokens) {
     uint64_t f = 0;
     for (uint32_t m = 0; m < n_mats; ++m) {
         uint32_t ks, kc;
-        const uint32_t base = base_ranges(mats[m].cols, tokens);
-        split_into(mats[m].cols, tokens <= kFewTokens ? base : 2 * base, &ks, &kc);
+        split_into(mats[m].cols, most_ranges(mats[m].cols, tokens), &ks, &kc);
         if (ks > 1) f += static_cast<uint64_t>(mats[m].rows) * ks * tokens;
     }
     return f;
@@ -626,8 +710,9 @@ int plan(const uint16_t *weights, uint64_t n_weights, const df11_matrix *mats, u
             return DF11_E_INVALID_ARG;
     }
     const bool few = tokens <= kRowsTokens;
-    uint32_t ks_req[kMax] = {};
-    if (!few && (rc = choose_ranges(mats, n_mats, tokens, ks_req)) != DF11_OK) return rc;
+    uint32_t ks_req[kMax];
+    rc = few ? split_rows(mats, n_mats, tokens, ks_req) : choose_ranges(mats, n_mats, tokens, ks_req);
+    if (rc) return rc;
 
     GemmArgs g{};
     ReduceArgs r{};
@@ -639,21 +724,17 @@ int plan(const uint16_t *weights, uint64_t n_weights, const df11_matrix *mats, u
     uint64_t wgs = 0, part = 0, outs = 0;
     uint32_t order[kMax];  // the matrices as they are launched
     for (uint32_t m = 0; m < n_mats; ++m) order[m] = m;
-    // a workgroup of the rows kernel takes as long as its row is: the longest
+    // a workgroup of the rows kernel takes as long as its columns are: the most
     // first, so that the launch does not end on them
     if (few)
-        std::stable_sort(order, order + n_mats,
-                         [&](uint32_t p, uint32_t q) { return mats[p].cols > mats[q].cols; });
+        std::stable_sort(order, order + n_mats, [&](uint32_t p, uint32_t q) {
+            return mats[p].cols / ks_req[p] > mats[q].cols / ks_req[q];
+        });
     for (uint32_t i = 0; i < n_mats; ++i) {
         const uint32_t m = order[i];
         const df11_matrix &d = mats[m];
         uint32_t ks, kc;
-        if (few) {
-            ks = 1;
-            kc = rows_range(d.cols);
-        } else {
-            split_into(d.cols, ks_req[m], &ks, &kc);
-        }
+        split_into(d.cols, ks_req[m], &ks, &kc);
         g.wg_start[i] = static_cast<uint32_t>(wgs);
         g.ksplit[i] = r.ksplit[i] = ks;
         g.kchunk[i] = kc;
@@ -664,8 +745,8 @@ int plan(const uint16_t *weights, uint64_t n_weights, const df11_matrix *mats, u
         g.x[i] = x[m];
         g.y[i] = r.y[i] = y[m];
         r.out_start[i] = static_cast<uint32_t>(outs);
-        wgs += few ? static_cast<uint64_t>(d.rows / kTileRows)
-                   : static_cast<uint64_t>((d.rows + kTileRows * kSlabWaves - 1) / (kTileRows * kSlabWaves)) * ks;
+        const uint32_t tile = kTileRows * (few ? 1u : kSlabWaves);  // features per workgroup
+        wgs += (uint64_t{d.rows} + tile - 1) / tile * ks;
         if (ks > 1) {
             part += static_cast<uint64_t>(d.rows) * ks * tokens;
             outs += static_cast<uint64_t>(d.rows) * tokens;

@@ -1,6 +1,7 @@
 // How the waves of a workgroup walk the columns of their rows in the products
-// for up to 16 tokens.  Plain integer arithmetic, shared with a host-side check;
-// no sum goes past the end, so that rows of close to 2^32 columns end too.
+// for up to 16 tokens.  Plain integer arithmetic, shared with a host-side check.
+// A workgroup counts columns from its first one on and holds at most 2^31 of
+// them (longer rows are always split), so no sum here wraps.
 #pragma once
 #include <cstdint>
 
@@ -24,6 +25,9 @@ DF11_HD uint32_t rows_range(uint32_t cols) {
     return quarter < kRangeCols ? quarter : kRangeCols;
 }
 
+// Fewest workgroups that a row of `cols` columns is split over.
+DF11_HD uint32_t least_ranges(uint32_t cols) { return cols > 0x80000000u ? 2u : 1u; }
+
 // First column past `n` from `at` on, at most `end` (at <= end).
 DF11_HD uint32_t past(uint32_t at, uint32_t n, uint32_t end) { return end - at > n ? at + n : end; }
 
@@ -32,28 +36,24 @@ struct Slab {
     uint32_t k0, k1, k;
 };
 
-// The wave's first slab; false when it has none.
-DF11_HD bool first_slab(uint32_t begin, uint32_t end, uint32_t range, uint32_t wave, Slab *s) {
-    s->k0 = s->k = past(begin, wave * range, end);
-    s->k1 = past(s->k0, range, end);
+// The wave's first slab of [0, end); false when it has none.
+DF11_HD bool first_slab(uint32_t end, uint32_t range, uint32_t wave, Slab *s) {
+    s->k0 = s->k = wave * range;
+    s->k1 = s->k0 + range < end ? s->k0 + range : end;
     return s->k0 < end;
 }
 
 // The range ends with this slab.
-DF11_HD bool last_of_range(const Slab &s) { return s.k1 - s.k <= kSlabCols; }
+DF11_HD bool last_of_range(const Slab &s) { return s.k + kSlabCols >= s.k1; }
 
 // The slab after s: in the range, or the first one of the wave's next range;
 // false when there is none.
 DF11_HD bool next_slab(uint32_t end, uint32_t range, const Slab &s, Slab *n) {
-    *n = s;
-    if (!last_of_range(s)) {
-        n->k = s.k + kSlabCols;
-        return true;
-    }
-    if (end - s.k0 <= kRowsWaves * range) return false;
-    n->k0 = n->k = s.k0 + kRowsWaves * range;
-    n->k1 = past(n->k0, range, end);
-    return true;
+    const bool turn = last_of_range(s);
+    n->k0 = turn ? s.k0 + kRowsWaves * range : s.k0;
+    n->k = turn ? n->k0 : s.k + kSlabCols;
+    n->k1 = n->k0 + range < end ? n->k0 + range : end;
+    return n->k < end;
 }
 
 }  // namespace df11gemm

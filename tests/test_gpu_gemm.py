@@ -173,3 +173,26 @@ def test_whole_rows_in_one_workgroup(tokens, cols):
     import torch
     check_against_oracle(w, mats, xs, run_gemm(
         torch.from_numpy(w.view(np.int16)).cuda().view(torch.bfloat16), mats, xs))
+
+
+@pytest.mark.parametrize("tokens", [1, 8, 9, 16])
+@pytest.mark.parametrize("shapes,split", [
+    ([(16, 65536)], True), ([(64, 14336), (16, 512)], True), ([(16, 512), (48, 8256), (32, 9984)], True),
+    ([(64, 8192)], False), ([(2048, 14336)], True), ([(2064, 14336)], False)],
+    ids=lambda v: "+".join(f"{r}x{c}" for r, c in v) if isinstance(v, list) else "")
+def test_long_rows_of_small_lists_are_split(shapes, split, tokens):
+    """Up to 16 tokens, long rows are split while the list's workgroups find a CU
+    each (one per 16 rows and range; 256 CUs), at the edges of that rule; the
+    split writes the workspace, whole rows do not."""
+    import torch
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the sizes are those of 256 CUs")
+    w, mats = make_block(shapes, tokens + len(shapes))
+    xs_h = [synth.activations(tokens, c, 72, i, tokens) for i, (_, _, c) in enumerate(mats)]
+    xs = [torch.from_numpy(x.view(np.int16)).cuda().view(torch.bfloat16) for x in xs_h]
+    ys = [torch.full((tokens, r), float("nan"), device="cuda") for _, r, _ in mats]
+    ws = torch.full((codec.gemm_workspace_bytes(mats, tokens) // 4,), float("nan"), device="cuda")
+    codec.block_gemm(torch.from_numpy(w.view(np.int16)).cuda().view(torch.bfloat16), mats, xs, ys, ws)
+    torch.cuda.synchronize()
+    assert bool((~torch.isnan(ws)).any()) == split
+    check_against_oracle(w, mats, xs_h, [y.cpu().numpy() for y in ys])
