@@ -79,6 +79,12 @@ struct GemvArgs {
     uint32_t x_at[kMaxM];      // where in LDS (kNotStaged: not there)
     uint32_t x_bytes;          // LDS for activations
     uint32_t boundary_grid;    // workgroups for the blocks at matrix boundaries
+    // where matrices start and end inside the stream, ascending, each position
+    // once; and the first matrix that a block around it can touch (a matrix is
+    // at least as long as a block, so there is at most one more, the next)
+    uint32_t n_bounds;
+    uint32_t bound[2 * kMaxM];
+    uint32_t bound_mat[2 * kMaxM];
     float *part;               // kSlots floats per block
     uint32_t *first_block;     // per row: the block holding its first weight
     uint32_t *last_block;      // per row: the block holding its last weight
@@ -128,17 +134,18 @@ __device__ __forceinline__ float dot8(const uint4 &w, const uint4 &x) {
 }
 
 // One block's weights [s, e) -- buffer bytes [lo_at, hi_at) from weight g0 on
-// -- times the activations of the (at most two) matrices they belong to, one
-// weight per lane and step: segment 0 is the matrix holding weight s, segment
-// 1 the first matrix that starts inside (s, e).  For the few blocks at the
-// matrices' boundaries; small rather than fast.
+// -- times the activations of the (at most two) matrices they belong to, m0 and
+// the next one, one weight per lane and step: segment 0 is the matrix holding
+// weight s, segment 1 the first matrix that starts inside (s, e).  For the few
+// blocks at the matrices' boundaries.
+constexpr uint32_t kAhead = 8;
 __device__ __forceinline__ void dot_block(const GemvArgs &g, uint32_t g0, uint32_t lo_at,
                                           uint32_t hi_at, const uint8_t *buf, uint32_t lane,
-                                          uint32_t b) {
+                                          uint32_t b, uint32_t m0) {
     const uint32_t s = g0 + lo_at, e = g0 + hi_at;
     bool inside = false;
 #pragma unroll 1
-    for (uint32_t m = 0; m < g.n_mats; ++m) {
+    for (uint32_t m = m0; m < umin(m0 + 2u, g.n_mats); ++m) {
         const uint32_t off = g.off[m], cols = g.cols[m];
         const uint32_t lo = umax(s, off), hi = umin(e, g.end[m]);
         if (lo >= hi || (off > s && inside)) continue;
@@ -151,13 +158,27 @@ __device__ __forceinline__ void dot_block(const GemvArgs &g, uint32_t g0, uint32
             const uint64_t start = uint64_t{off} + uint64_t{row} * cols;
             const uint32_t stop = static_cast<uint32_t>(umin64(hi, start + cols));
             float sum = 0.f;
+            // kAhead weights of a lane requested at once (from memory, one after
+            // the other they were the whole time of a short call)
+            const uint32_t last = stop - 1u - at;
 #pragma unroll 1
-            for (uint32_t q = at + lane; q < stop && q >= at; q += 64u) {
-                const uint32_t sm = g.d.sm[q], ex = buf[q - g0];
-                const uint32_t w = ((sm & 0x80u) << 24) | ((ex & 0x7Fu) << 24) |
-                                   ((ex & 0x80u) << 16) | ((sm & 0x7Fu) << 16);
-                const uint32_t x = g.x[m][q - static_cast<uint32_t>(start)];
-                sum += __builtin_bit_cast(float, w) * __builtin_bit_cast(float, x << 16);
+            for (uint32_t q0 = lane; q0 <= last; q0 += 64u * kAhead) {
+                uint32_t sm[kAhead], x[kAhead];
+#pragma unroll
+                for (uint32_t k = 0; k < kAhead; ++k) {
+                    const uint32_t q = at + umin(q0 + 64u * k, last);
+                    sm[k] = g.d.sm[q];
+                    x[k] = g.x[m][q - static_cast<uint32_t>(start)];
+                }
+#pragma unroll
+                for (uint32_t k = 0; k < kAhead; ++k) {
+                    const uint32_t q = umin(q0 + 64u * k, last);
+                    const uint32_t ex = buf[at + q - g0];
+                    const uint32_t w = ((sm[k] & 0x80u) << 24) | ((ex & 0x7Fu) << 24) |
+                                       ((ex & 0x80u) << 16) | ((sm[k] & 0x7Fu) << 16);
+                    const float v = __builtin_bit_cast(float, w) * __builtin_bit_cast(float, x[k] << 16);
+                    sum += q0 + 64u * k <= last ? v : 0.f;
+                }
             }
             sum = wave_sum(sum);
             if (lane == 63u) {
@@ -295,13 +316,18 @@ __device__ __forceinline__ void dot_plain(const GemvArgs &g, const Range &r, con
         for (int k = 0; k < kPre; ++k) add(d[k], gr.at[k]);
         add(d[kPre], el);
     }
+    // blocks of more than 2048 weights (codes of less than two bits on average)
 #pragma unroll 1
-    for (uint32_t gi = lane + 64u * kPre; __builtin_expect(gi < r.full_hi, 0); gi += 64u) {
-        const uint32_t at = gi << 3;
-        add(dot8(assemble_group(reinterpret_cast<const uint2 *>(buf)[gi],
-                                *reinterpret_cast<const uint2 *>(g.d.sm + r.g0 + at)),
-                 load_x8(staged, cur.x, in_lds, span_column(sp, at))),
-            at);
+    for (uint32_t base = 64u * kPre; __builtin_expect(base < r.full_hi, 0); base += 64u * kPre) {
+        const Groups<kPre> more = block_groups<kPre>(r, base + lane, 64u);
+        uint2 T[kPre];
+        prefetch_sm(g.d, r, more, T);
+#pragma unroll
+        for (int k = 0; k < kPre; ++k) {
+            const float v = dot8(assemble_group(*reinterpret_cast<const uint2 *>(buf + more.at[k]), T[k]),
+                                 load_x8(staged, cur.x, in_lds, span_column(sp, more.at[k])));
+            add(full_group(r, base + lane + 64u * k) ? v : 0.f, more.at[k]);
+        }
     }
     t[0] = wave_sum(t[0]);
     if (sp.nrows > 1u) t[1] = wave_sum(t[1]);
@@ -332,27 +358,19 @@ __device__ __forceinline__ uint32_t find_block(const DecodeArgs &a, uint32_t pos
     return lo;
 }
 
-// Where a matrix starts (q even) or ends (q odd).
-__device__ __forceinline__ uint32_t boundary(const GemvArgs &g, uint32_t q) {
-    return (q & 1u) ? g.end[q >> 1] : g.off[q >> 1];
-}
-
 // The block that has boundary q inside it (the first of its boundaries takes
 // it): decoded by one wave like any other, multiplied by dot_block.
 __device__ __forceinline__ void boundary_block(const GemvArgs &g, const Tables &tb, uint8_t *lds,
                                                uint32_t buf_off, uint32_t lane, uint32_t q) {
     const DecodeArgs &a = g.d;
-    const uint32_t pos = boundary(g, q);
-    if (pos >= a.n_elems) return;
+    const uint32_t pos = g.bound[q], before = q ? g.bound[q - 1u] : 0u;
     const uint32_t b = static_cast<uint32_t>(
         __builtin_amdgcn_readfirstlane(static_cast<int>(find_block(a, pos, lane))));
     const ChunkWords cw = load_chunk<64>(a, b, lane);
     const Chunk ch[1] = {chunk_setup<64>(a, cw, b, lane)};
     const Range r = block_range(a, cw);
     const uint32_t s = r.g0 + r.shift, e = r.g0 + r.lim;
-    if (pos <= s || pos >= e) return;
-    for (uint32_t i = 0; i < q; ++i)
-        if (boundary(g, i) > s && boundary(g, i) < e) return;
+    if (pos <= s || pos >= e || before > s) return;  // (they ascend)
     for (uint32_t i = lane; i < (a.buf_bytes >> 4); i += 64u)
         reinterpret_cast<uint4 *>(lds + buf_off)[i] = make_uint4(0u, 0u, 0u, 0u);
     Trail<kKeep> tr[1];
@@ -362,7 +380,7 @@ __device__ __forceinline__ void boundary_block(const GemvArgs &g, const Tables &
     wave_lds_sync();
     emit_exponents(tb, ch[0], tr[0], state[0], 8u * r.shift + excl8, buf_off, a.buf_bytes);
     wave_lds_sync();
-    dot_block(g, r.g0, r.shift, r.lim, lds + buf_off + kBufLead, lane, b);
+    dot_block(g, r.g0, r.shift, r.lim, lds + buf_off + kBufLead, lane, b, g.bound_mat[q]);
 }
 
 // Same loop as the decode kernel's for 64-chunk blocks (persistent grid, one
@@ -396,7 +414,7 @@ df11_gemv_wave_kernel(GemvArgs g) {
         __syncthreads();
         const Tables tb = staged_tables(a, lds);
         const uint32_t q = blockIdx.x * W + wave;
-        if (q < 2u * g.n_mats)
+        if (q < g.n_bounds)
             boundary_block(g, tb, lds, a.table_lds_bytes + g.x_bytes + wave * a.buf_bytes, lane, q);
         return;
     }
@@ -743,7 +761,17 @@ int df11_block_gemv(const df11_stream *dev, const df11_matrix *mats, uint32_t n_
     g.x_bytes = assign_x_sets(mats, n_mats, &g);
     rc = gemv_shape(a.table_lds_bytes + g.x_bytes, a.buf_bytes, &W, &grid_max);
     if (rc) return rc;
-    g.boundary_grid = (2u * n_mats + W - 1) / W;
+    for (uint32_t m = 0; m < n_mats; ++m) {
+        if (g.off[m] > 0 && (m == 0 || g.off[m] > g.end[m - 1])) {
+            g.bound[g.n_bounds] = g.off[m];
+            g.bound_mat[g.n_bounds++] = m ? m - 1 : 0;
+        }
+        if (g.end[m] < a.n_elems) {
+            g.bound[g.n_bounds] = g.end[m];
+            g.bound_mat[g.n_bounds++] = m;
+        }
+    }
+    g.boundary_grid = (g.n_bounds + W - 1) / W;
     uint32_t grid = (a.num_blocks + W - 1) / W;
     const uint32_t room = grid_max > g.boundary_grid ? grid_max - g.boundary_grid : 1u;
     if (grid > room) grid = room;

@@ -186,3 +186,17 @@ def test_block_gemv_staged_activations(shapes, repeat):
     ds = codec.to_device(codec.encode(w, layout=FUSED), "cuda")
     xs_h = [synth.activations(1, c, 61, i) for i, (_, _, c) in enumerate(mats)]
     check_oracle(w, mats, xs_h, run_gemv(ds, mats, xs_h))
+
+
+@pytest.mark.parametrize("gaps", [(0,) * 8, (0, 8, 0, 16, 4088, 0, 4096, 8), (24, 0, 8, 8, 8, 8, 8, 8)],
+                         ids=["adjacent", "mixed", "close"])
+@pytest.mark.parametrize("const", [None, 0x3F80], ids=["gaussian", "one_symbol"])
+def test_block_gemv_at_the_boundaries_of_the_smallest_matrices(gaps, const):
+    """Matrices of 4096 weights, as long as the largest block: nearly every block
+    has a boundary inside it, some an end and a start, some a whole gap; with
+    one symbol the blocks are full and span rows and matrices alike."""
+    w, mats = make_stream([(2, 2048)] * 8, 5 + sum(gaps), gaps=gaps, const=const)
+    w = np.concatenate([w, synth.gaussian(40, 0.02, 3)])  # and weights after the last one
+    ds = codec.to_device(codec.encode(w, layout=FUSED), "cuda")
+    xs_h = [synth.activations(1, c, 62, i) for i, (_, _, c) in enumerate(mats)]
+    check_oracle(w, mats, xs_h, run_gemv(ds, mats, xs_h))
