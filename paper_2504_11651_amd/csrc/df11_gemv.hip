@@ -36,8 +36,6 @@ constexpr uint32_t kSlots = 2 * kSegSlots;     // per block
 constexpr uint32_t kMinCols = 2048;            // a block (<= 4096 weights) spans <= 3 rows
 constexpr uint32_t kMaxBlockElems = 64u * 64u; // 64 chunks of at most 64 codes
 
-constexpr uint32_t kNotStaged = 0xFFFFFFFFu;
-
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ uint64_t umin64(uint64_t a, uint64_t b) { return a < b ? a : b; }
@@ -75,9 +73,6 @@ struct GemvArgs {
     Divider div[kMaxM];   // division by cols
     const uint16_t *x[kMaxM];
     uint32_t row_base[kMaxM];  // index of the matrix's first row among all rows
-    uint32_t x_set[kMaxM];     // activations staged in LDS together: 1, 2, ... in matrix order
-    uint32_t x_at[kMaxM];      // where in LDS (kNotStaged: not there)
-    uint32_t x_bytes;          // LDS for activations
     uint32_t boundary_grid;    // workgroups for the blocks at matrix boundaries
     // where matrices start and end inside the stream, ascending, each position
     // once; and the first matrix that a block around it can touch (a matrix is
@@ -197,7 +192,7 @@ __device__ __forceinline__ void dot_block(const GemvArgs &g, uint32_t g0, uint32
 struct Current {
     uint32_t next;      // index of the next matrix
     uint32_t next_off;  // its first weight
-    uint32_t off, end, cols, row_base, x_at, x_set;
+    uint32_t off, end, cols, row_base;
     Divider div;
     const uint16_t *x;
 };
@@ -215,8 +210,6 @@ __device__ __forceinline__ void advance(const GemvArgs &g, uint32_t s, Current &
         cur.end = g.end[m];
         cur.cols = g.cols[m];
         cur.row_base = g.row_base[m];
-        cur.x_at = g.x_at[m];
-        cur.x_set = g.x_set[m];
         cur.div = g.div[m];
         cur.x = g.x[m];
     }
@@ -252,37 +245,22 @@ __device__ __forceinline__ uint32_t span_column(const Span &sp, uint32_t at) {
     return umin(c, c - sp.cols);
 }
 
-// 8 activations from column c on: from LDS where they are staged.
-__device__ __forceinline__ uint4 load_x8(const uint8_t *staged, const uint16_t *x, bool in_lds,
-                                         uint32_t c) {
-    if (in_lds) return *reinterpret_cast<const uint4 *>(staged + 2u * c);
-    return *reinterpret_cast<const uint4 *>(x + c);
-}
-
 // A plain block's weights times their activations: whole groups eight at a
 // time; the elements of the (at most two) groups shared with the neighbours
 // one per lane.
 __device__ __forceinline__ void dot_plain(const GemvArgs &g, const Range &r, const Current &cur,
-                                          const Span &sp, const uint8_t *buf, const uint8_t *staged,
-                                          bool in_lds, uint32_t lane, const Groups<kPre> &gr,
-                                          const uint2 (&S)[kPre], uint32_t edge_sm, uint32_t b) {
+                                          const Span &sp, const uint8_t *buf, uint32_t lane,
+                                          const Groups<kPre> &gr, const uint2 (&S)[kPre],
+                                          uint32_t edge_sm, uint32_t b) {
     const uint32_t el = edge_byte(r, lane & 15u);
     uint2 E[kPre];
     uint4 X[kPre];
 #pragma unroll
     for (int k = 0; k < kPre; ++k) E[k] = *reinterpret_cast<const uint2 *>(buf + gr.at[k]);
-    uint32_t edge_x;
-    if (__builtin_expect(in_lds, 1)) {  // uniform
 #pragma unroll
-        for (int k = 0; k < kPre; ++k)
-            X[k] = *reinterpret_cast<const uint4 *>(staged + 2u * span_column(sp, gr.at[k]));
-        edge_x = *reinterpret_cast<const uint16_t *>(staged + 2u * span_column(sp, el));
-    } else {
-#pragma unroll
-        for (int k = 0; k < kPre; ++k)
-            X[k] = *reinterpret_cast<const uint4 *>(cur.x + span_column(sp, gr.at[k]));
-        edge_x = cur.x[span_column(sp, el)];
-    }
+    for (int k = 0; k < kPre; ++k)
+        X[k] = *reinterpret_cast<const uint4 *>(cur.x + span_column(sp, gr.at[k]));
+    const uint32_t edge_x = cur.x[span_column(sp, el)];
     const uint32_t edge_e = buf[el];
     float t[3] = {0.f, 0.f, 0.f};
     // (rows past the block's are never reached: c stays below their start)
@@ -325,7 +303,7 @@ __device__ __forceinline__ void dot_plain(const GemvArgs &g, const Range &r, con
 #pragma unroll
         for (int k = 0; k < kPre; ++k) {
             const float v = dot8(assemble_group(*reinterpret_cast<const uint2 *>(buf + more.at[k]), T[k]),
-                                 load_x8(staged, cur.x, in_lds, span_column(sp, more.at[k])));
+                                 *reinterpret_cast<const uint4 *>(cur.x + span_column(sp, more.at[k])));
             add(full_group(r, base + lane + 64u * k) ? v : 0.f, more.at[k]);
         }
     }
@@ -385,12 +363,11 @@ __device__ __forceinline__ void boundary_block(const GemvArgs &g, const Tables &
 
 // Same loop as the decode kernel's for 64-chunk blocks (persistent grid, one
 // wave per block); the decoded weights go into their dot products instead of
-// memory.  The activations are staged in LDS, as many matrices' at once as
-// its part for them holds: read through the caches they are three times the
-// stream's own bytes, and the streaming data evicts them from the L1.  A
-// workgroup takes W neighbouring blocks per round and stages the next set
-// when the first of them reaches it; the few blocks of a round that are
-// already past the staged set read their activations from memory.
+// memory.  The activations are read through the caches.  (Staged in LDS, one
+// set of matrices after the other, they cost scalar registers, LDS and a round
+// trip per matrix, and were slower at every size: 8 matrices of 256 x 2048 14.4
+// us against 13.5, of 2048 x 2048 31.0 against 26.2, a Llama-3-8B-sized block
+// 115 against 109.5.)
 //
 // The blocks at the matrices' boundaries go to the first workgroups, a wave
 // each: in the loop, their code would cost every block scalar registers
@@ -398,8 +375,8 @@ __device__ __forceinline__ void boundary_block(const GemvArgs &g, const Tables &
 //
 // Bound: instruction issue and latency -- about 400 vector and 280 scalar
 // instructions per block, six waves per SIMD.  A Llama-3-8B-sized block's
-// compressed bytes alone take 57 us at the rate of a device copy; 153 us
-// before and 119 us now for the two kernels.
+// compressed bytes alone take 57 us at the rate of a device copy; 109.5 us
+// for the two kernels.
 template <uint32_t W>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) void
 df11_gemv_wave_kernel(GemvArgs g) {
@@ -409,63 +386,30 @@ df11_gemv_wave_kernel(GemvArgs g) {
     const uint32_t lane = tid & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // block indices stay scalar
     const uint32_t main_grid = gridDim.x - g.boundary_grid;
+    const uint32_t buf_off = a.table_lds_bytes + wave * a.buf_bytes;
     if (blockIdx.x < g.boundary_grid) {
         stage_table_blob(a, lds, tid, 64 * W);
         __syncthreads();
         const Tables tb = staged_tables(a, lds);
         const uint32_t q = blockIdx.x * W + wave;
-        if (q < g.n_bounds)
-            boundary_block(g, tb, lds, a.table_lds_bytes + g.x_bytes + wave * a.buf_bytes, lane, q);
+        if (q < g.n_bounds) boundary_block(g, tb, lds, buf_off, lane, q);
         return;
     }
-    const uint32_t first_group = xcd_grouped_index(blockIdx.x - g.boundary_grid, main_grid) * W;
+    const uint32_t first_block = xcd_grouped_index(blockIdx.x - g.boundary_grid, main_grid) * W + wave;
     const uint32_t stride = main_grid * W;
     ChunkWords cw{};
-    uint32_t group_pos = 0;  // first weight of the round's first block
-    if (first_group + wave < a.num_blocks) cw = load_chunk<64>(a, first_group + wave, lane);
-    if (first_group < a.num_blocks) group_pos = block_positions(a)[first_group];
+    if (first_block < a.num_blocks) cw = load_chunk<64>(a, first_block, lane);
     stage_table_blob(a, lds, tid, 64 * W);
-    uint8_t *xs = lds + a.table_lds_bytes;
-    const uint32_t buf_off = a.table_lds_bytes + g.x_bytes + wave * a.buf_bytes;
     uint8_t *buf = lds + buf_off + kBufLead;
     __syncthreads();
+    if (first_block >= a.num_blocks) return;
     const Tables tb = staged_tables(a, lds);
-    Chunk ch[1] = {chunk_setup<64>(a, cw, first_group + wave, lane)};
+    Chunk ch[1] = {chunk_setup<64>(a, cw, first_block, lane)};
     Range r = block_range(a, cw);
     Current cur{};
     cur.next_off = matrix_start(g, 0u);
-    uint32_t set = 0, next_set = 0;        // staged set (none yet: 0), and where the next begins
-    uint32_t next_set_mat = 0;
-    next_set = matrix_start(g, 0u);
 
-    for (uint32_t group = first_group; group < a.num_blocks; group += stride) {
-        // (uniform over the workgroup: every wave sees the same positions)
-        if (__builtin_expect(group_pos >= next_set && next_set_mat < g.n_mats, 0)) {
-            uint32_t m = next_set_mat, found = 0;
-            // the set of the matrix holding group_pos: skip sets that end before it
-            while (next_set_mat < g.n_mats && group_pos >= matrix_start(g, next_set_mat)) {
-                if (g.x_set[next_set_mat] != found) {
-                    found = g.x_set[next_set_mat];
-                    m = next_set_mat;
-                }
-                ++next_set_mat;
-            }
-            while (next_set_mat < g.n_mats && g.x_set[next_set_mat] == found) ++next_set_mat;
-            next_set = matrix_start(g, next_set_mat);
-            set = found;
-            __syncthreads();  // the staged activations are no longer read
-            for (; m < next_set_mat; ++m) {
-                if (g.x_at[m] == kNotStaged) continue;
-                const uint4 *src = reinterpret_cast<const uint4 *>(g.x[m]);
-                uint4 *dst = reinterpret_cast<uint4 *>(xs + g.x_at[m]);
-                for (uint32_t i = tid; i < g.cols[m] / 8u; i += 64u * W) dst[i] = src[i];
-            }
-            __syncthreads();
-        }
-        const uint32_t b = group + wave;
-        const uint32_t gn = group + stride;
-        if (gn < a.num_blocks) group_pos = block_positions(a)[gn];
-        if (b >= a.num_blocks) continue;  // the last round's spare waves
+    for (uint32_t b = first_block; b < a.num_blocks; b += stride) {
         ChunkWords nxt = cw;
         if (b + stride < a.num_blocks) nxt = load_chunk<64>(a, b + stride, lane);
         const Groups<kPre> gr = block_groups<kPre>(r, lane, 64u);
@@ -489,9 +433,7 @@ df11_gemv_wave_kernel(GemvArgs g) {
         __builtin_amdgcn_s_setprio(2);
         advance(g, r.g0 + r.shift, cur);
         const Span sp = block_span(cur, r);
-        if (__builtin_expect(sp.plain, 1))
-            dot_plain(g, r, cur, sp, buf, xs + cur.x_at, cur.x_set == set && cur.x_at != kNotStaged,
-                      lane, gr, S, edge_sm, b);
+        if (__builtin_expect(sp.plain, 1)) dot_plain(g, r, cur, sp, buf, lane, gr, S, edge_sm, b);
         __builtin_amdgcn_s_setprio(0);
         cw = nxt;
         ch[0] = chunk_setup<64>(a, cw, b + stride, lane);
@@ -566,45 +508,19 @@ GemvFn gemv_kernel(uint32_t W) {
     }
 }
 
-// LDS for activations: matrices of up to 16384 columns one at a time, smaller
-// ones several (a Llama-3-8B-sized block's seven in three sets, so a
-// workgroup stops to stage them twice after its start).
-constexpr uint32_t kXBytes = 32768;
-
-uint32_t assign_x_sets(const df11_matrix *mats, uint32_t n_mats, GemvArgs *g) {
-    uint32_t set = 1, used = 0, most = 0;
-    for (uint32_t m = 0; m < n_mats; ++m) {
-        const uint64_t need = 2ull * mats[m].cols;
-        if (need > kXBytes) {
-            g->x_set[m] = set;
-            g->x_at[m] = kNotStaged;
-            continue;
-        }
-        if (used + need > kXBytes) {
-            ++set;
-            used = 0;
-        }
-        g->x_set[m] = set;
-        g->x_at[m] = used;
-        used += static_cast<uint32_t>(need);
-        if (used > most) most = used;
-    }
-    return most;
-}
-
 struct Shape {
     int dev;
-    uint32_t fixed, buf, W, per_cu;
+    uint32_t tables, buf, W, per_cu;
 };
 std::mutex g_mu;
 std::vector<Shape> g_shapes;
 std::vector<std::array<uint32_t, 4>> g_lds_granted;  // per device and kernel: dynamic LDS allowed
 constexpr size_t kMaxShapes = 64;
 
-// Workgroup size and resident workgroups per CU for `fixed` bytes of LDS per
+// Workgroup size and resident workgroups per CU for `tables` bytes of LDS per
 // workgroup and `buf` per wave: the most resident waves, fewer per workgroup
 // on a tie.
-int gemv_shape(uint32_t fixed, uint32_t buf, uint32_t *W_out, uint32_t *grid_max) {
+int gemv_shape(uint32_t tables, uint32_t buf, uint32_t *W_out, uint32_t *grid_max) {
     int dev = 0, cus = 0, max_lds = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -612,7 +528,7 @@ int gemv_shape(uint32_t fixed, uint32_t buf, uint32_t *W_out, uint32_t *grid_max
         return DF11_E_HIP;
     std::lock_guard<std::mutex> lk(g_mu);
     for (const Shape &sh : g_shapes) {
-        if (sh.dev == dev && sh.fixed == fixed && sh.buf == buf) {
+        if (sh.dev == dev && sh.tables == tables && sh.buf == buf) {
             *W_out = sh.W;
             *grid_max = sh.per_cu * static_cast<uint32_t>(cus);
             return DF11_OK;
@@ -623,7 +539,7 @@ int gemv_shape(uint32_t fixed, uint32_t buf, uint32_t *W_out, uint32_t *grid_max
     uint32_t best_W = 0, best_pc = 0, best_waves = 0;
     for (uint32_t i = 0; i < 4; ++i) {
         const uint32_t W = 4u * (i + 1u);
-        const uint32_t lds = fixed + W * buf;
+        const uint32_t lds = tables + W * buf;
         if (lds > static_cast<uint32_t>(max_lds)) continue;
         const void *fn = reinterpret_cast<const void *>(gemv_kernel(W));
         if (lds > 65536u && granted[i] < lds) {
@@ -636,6 +552,8 @@ int gemv_shape(uint32_t fixed, uint32_t buf, uint32_t *W_out, uint32_t *grid_max
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&pc, fn, static_cast<int>(64 * W), lds) !=
             hipSuccess)
             return DF11_E_HIP;
+        const uint32_t fits = lds_fit(static_cast<uint32_t>(max_lds), lds);
+        if (static_cast<uint32_t>(pc) > fits) pc = static_cast<int>(fits);
         if (static_cast<uint32_t>(pc) * W > best_waves) {
             best_waves = static_cast<uint32_t>(pc) * W;
             best_W = W;
@@ -644,7 +562,7 @@ int gemv_shape(uint32_t fixed, uint32_t buf, uint32_t *W_out, uint32_t *grid_max
     }
     if (!best_waves) return DF11_E_UNSUPPORTED;
     if (g_shapes.size() >= kMaxShapes) g_shapes.clear();
-    g_shapes.push_back(Shape{dev, fixed, buf, best_W, best_pc});
+    g_shapes.push_back(Shape{dev, tables, buf, best_W, best_pc});
     *W_out = best_W;
     *grid_max = best_pc * static_cast<uint32_t>(cus);
     return DF11_OK;
@@ -758,8 +676,7 @@ int df11_block_gemv(const df11_stream *dev, const df11_matrix *mats, uint32_t n_
     ra.last_block = g.last_block;
 
     uint32_t W = 0, grid_max = 0;
-    g.x_bytes = assign_x_sets(mats, n_mats, &g);
-    rc = gemv_shape(a.table_lds_bytes + g.x_bytes, a.buf_bytes, &W, &grid_max);
+    rc = gemv_shape(a.table_lds_bytes, a.buf_bytes, &W, &grid_max);
     if (rc) return rc;
     for (uint32_t m = 0; m < n_mats; ++m) {
         if (g.off[m] > 0 && (m == 0 || g.off[m] > g.end[m - 1])) {
@@ -777,7 +694,7 @@ int df11_block_gemv(const df11_stream *dev, const df11_matrix *mats, uint32_t n_
     if (grid > room) grid = room;
     if (!grid) grid = 1;
     grid += g.boundary_grid;
-    const uint32_t lds = a.table_lds_bytes + g.x_bytes + W * a.buf_bytes;
+    const uint32_t lds = a.table_lds_bytes + W * a.buf_bytes;
     hipLaunchKernelGGL(gemv_kernel(W), dim3(grid), dim3(64 * W), lds, stream, g);
     if (hipGetLastError() != hipSuccess) return DF11_E_HIP;
     hipLaunchKernelGGL(df11_gemv_reduce_kernel, dim3(static_cast<uint32_t>((rows * kRowLanes + 255) / 256)),

@@ -170,17 +170,16 @@ def test_gemv_on_a_side_stream_without_workspace():
 
 
 @pytest.mark.parametrize("shapes", [
-    # activations too wide for the LDS part (more than 16384 columns) between staged ones
+    # rows of more than 16384 columns between short ones
     [(8, 4096), (6, 16448), (8, 4096)],
-    # exactly the LDS part, one matrix per set
     [(5, 16384), (4, 16384), (16, 2048)],
-    # several matrices per set, sets that begin inside a round of blocks
+    # many matrices, several of them inside a round of blocks
     [(4, 8192), (3, 8192), (7, 2112), (2, 8192), (40, 4096), (5, 2048), (1, 8192), (9, 4160)],
 ], ids=["wide", "full", "sets"])
 @pytest.mark.parametrize("repeat", [1, 12])
 def test_block_gemv_staged_activations(shapes, repeat):
-    """Where a matrix's activations are staged, with one and with many rounds
-    of blocks per workgroup between the sets."""
+    """Activations of many widths, with one and with many rounds of blocks per
+    workgroup between the matrices."""
     shapes = [(r * repeat, c) for r, c in shapes]
     w, mats = make_stream(shapes, 77 + repeat)
     ds = codec.to_device(codec.encode(w, layout=FUSED), "cuda")
