@@ -88,6 +88,15 @@ struct ReduceArgs {
 
 __device__ __forceinline__ uint32_t umin(uint32_t a, uint32_t b) { return a < b ? a : b; }
 
+// Hands LDS over between the lanes of a wave: earlier accesses stay before later
+// ones.  LDS executes a wave's instructions in order, so this only holds the
+// compiler, which sees one lane's addresses at a time.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 __device__ __forceinline__ uint4 load16(const uint16_t *p) {
     return *reinterpret_cast<const uint4 *>(p);
 }
@@ -166,8 +175,8 @@ __device__ __forceinline__ void write_tile(const GemmArgs &a, const Mat &m, uint
 //
 // Weights and activations pass through LDS of the wave's own: a load
 // instruction reads 512 contiguous bytes of each of two rows (8 whole cache
-// lines) rather than 64 bytes of each of 16 rows, and nothing needs a barrier,
-// since one wave's LDS accesses complete in order.  Row r's 16-byte piece p of
+// lines) rather than 64 bytes of each of 16 rows, and nothing needs a workgroup
+// barrier, since one wave's LDS accesses complete in order.  Row r's 16-byte piece p of
 // the weights lies at slot (p + r) mod 32 and the activation rows are padded by
 // 16 bytes, so reads have no bank conflicts.
 //
@@ -259,6 +268,7 @@ __global__ __launch_bounds__(64 * kWaves) void gemm_rows_kernel(GemmArgs a) {
             const uint32_t at = piece(nx.k, nx.k1);
             // each register takes the next slab's load as soon as it is in
             // LDS, so a slab of weights stays in flight
+            wave_lds_sync();  // the slab before is read
             put_x();
             __builtin_amdgcn_sched_barrier(0);
             load_x(at);
@@ -269,6 +279,7 @@ __global__ __launch_bounds__(64 * kWaves) void gemm_rows_kernel(GemmArgs a) {
                 load_w(i, at);
                 __builtin_amdgcn_sched_barrier(0);
             }
+            wave_lds_sync();
             const uint32_t steps = umin(kUnroll, (sl.k1 - sl.k) / kKStep);  // uniform
 #pragma unroll
             for (uint32_t u = 0; u < kUnroll; ++u)
@@ -283,9 +294,11 @@ __global__ __launch_bounds__(64 * kWaves) void gemm_rows_kernel(GemmArgs a) {
             sl = nx;
         }
         const uint32_t steps = umin(kUnroll, (sl.k1 - sl.k) / kKStep);
+        wave_lds_sync();
         put_x();
 #pragma unroll
         for (uint32_t i = 0; i < 8; ++i) put_w(i);
+        wave_lds_sync();
 #pragma unroll
         for (uint32_t u = 0; u < kUnroll; ++u)
             if (u < steps) products(u);
@@ -437,6 +450,7 @@ gemm_slab_kernel(GemmArgs a) {
             load_w(i, kn);
             __builtin_amdgcn_sched_barrier(0);
         }
+        wave_lds_sync();
 #pragma unroll
         for (uint32_t u = 0; u < kUnroll; ++u)
             if (active) products(u);
@@ -448,6 +462,7 @@ gemm_slab_kernel(GemmArgs a) {
     const uint32_t steps = umin(kUnroll, (k1 - k) / kKStep);  // uniform
 #pragma unroll
     for (uint32_t i = 0; i < 8; ++i) put_w(i);
+    wave_lds_sync();
 #pragma unroll
     for (uint32_t u = 0; u < kUnroll; ++u)
         if (active && u < steps) products(u);

@@ -45,3 +45,30 @@ def test_tables_come_from_lds_after_the_barrier():
                 staged = barrier = False
                 seen += 1
     assert seen == 6  # four decode kernels, the fused kernel's two paths
+
+
+def test_lanes_hand_lds_over_in_the_products():
+    """Weights (and up to 16 tokens activations) are written to LDS by some lanes
+    of a wave and read by others: the writes come before the reads, and the reads
+    before the next writes, by more than the compiler's view of one lane."""
+    text = source("df11_gemm.hip")
+    for kernel in ("gemm_rows_kernel(", "gemm_slab_kernel("):
+        code = body(text, kernel)
+        code = re.sub(r"auto \w+ = \[&\].*?\n    \};", "", code, flags=re.S)  # the lambdas
+        calls = re.findall(r"\b(put_x|put_w|products|wave_lds_sync|__syncthreads|for \(;;\)|"
+                           r"for \(; k1)", code)
+        # the loop's body twice, so that its back edge is seen too
+        at = next(i for i, c in enumerate(calls) if c.startswith("for"))
+        end = calls.index("products", at) + 1
+        while end < len(calls) and calls[end] == "__syncthreads":
+            end += 1
+        order = calls[:at] + 2 * calls[at + 1:end] + calls[end:]
+        assert order.count("products") == 3 and order.count("put_w") == 3, (kernel, order)
+        last = None
+        for call in order:
+            if call in ("wave_lds_sync", "__syncthreads"):
+                last = None
+                continue
+            now = "read" if call == "products" else "write"
+            assert last in (None, now), f"{kernel} {last} then {call} without a hand-over: {order}"
+            last = now
