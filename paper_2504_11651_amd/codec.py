@@ -280,7 +280,6 @@ class DeviceStream:
         self._st = Stream(self.exp.data_ptr(), self.sm.data_ptr(), self.gaps.data_ptr(),
                           self.block_pos.data_ptr(), self.tables.data_ptr(), self.sizes,
                           self.layout)
-        self._ref = ctypes.byref(self._st)
 
     @property
     def n_elems(self) -> int:
@@ -323,11 +322,9 @@ def decode_block(ds: DeviceStream, out=None, stream=None):
     if out.numel() < n or out.element_size() != 2 or not out.is_contiguous():
         raise ValueError("out must be a contiguous 2-byte tensor with n_elems elements")
     _on_device(out, ds.device, "out")
-    # plain integers: the declared argument types convert them, and a small
-    # stream's decode takes about as long as this call
-    rc = (_lib or lib()).df11_decode_block(ds._ref, out.data_ptr(), _handle(stream, ds.device))
-    if rc:
-        _check(rc, "df11_decode_block")
+    # plain integers: the declared argument types convert them
+    _check((_lib or lib()).df11_decode_block(ctypes.byref(ds.struct()), out.data_ptr(),
+                                             _handle(stream, ds.device)), "df11_decode_block")
     return out
 
 

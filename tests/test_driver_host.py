@@ -17,8 +17,7 @@ def llama_mats():
 
 
 def test_workspace_closed_form():
-    # up to 8 tokens every matrix is split into k ranges of 1024 columns
-    # (4 for the 4096-column matrices, 14 for down); partial sums of rows x
+    # up to 8 tokens the workspace holds k ranges of 1024 columns (4 for the 4096-column matrices, 14 for down); partial sums of rows x
     # ranges x tokens floats
     mats, _ = llama_mats()
     few = 4 * (4096 + 1024 + 1024 + 4096 + 14336 + 14336) + 14 * 4096
@@ -200,3 +199,27 @@ def test_binding_refuses_host_tensors():
         codec.block_gemm(weights, [(0, 16, 64)], [x], [y])
     with pytest.raises(ValueError):
         codec.block_gemm(weights, [], [], [])
+
+
+def test_decode_block_takes_the_stream_the_object_gives(monkeypatch):
+    """decode_block asks the object for its stream: one that presents another
+    stream (a view, a wrapper) decodes that one."""
+    import torch
+    st, seen = codec.Stream(), []
+
+    class View:
+        n_elems, device = 8, torch.device("cpu")
+
+        def struct(self):
+            return st
+
+    class Lib:
+        @staticmethod
+        def df11_decode_block(ref, out, stream):
+            seen.append((ref._obj, out, stream))
+            return codec.DF11_OK
+
+    monkeypatch.setattr(codec, "_lib", Lib)
+    out = torch.empty(8, dtype=torch.bfloat16)
+    assert codec.decode_block(View(), out, stream=0) is out
+    assert seen == [(st, out.data_ptr(), 0)] and seen[0][0] is st
