@@ -84,7 +84,7 @@ __global__ __launch_bounds__(64 * W) void df11_decode_wave_kernel(DecodeArgs a) 
         prefetch_sm(a, r, gr, S);
         const uint32_t edge_sm = prefetch_edge_sm(a, r, lane);
 
-        if (a.hold) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");  // as below, 5 issued
+        if (a.hold) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");  // as below, 5 loads
         wave_lds_sync();  // this wave's reads of the previous block are issued
         for (uint32_t i = lane; i < (a.buf_bytes >> 4); i += 64u)
             reinterpret_cast<uint4 *>(lds + buf_off)[i] = make_uint4(0u, 0u, 0u, 0u);
@@ -147,9 +147,10 @@ __global__ __launch_bounds__(64 * W) void df11_decode_pair_kernel(DecodeArgs a) 
         uint2 S[kPrePair];
         prefetch_sm(a, r, gr, S);
         const uint32_t edge_sm = prefetch_edge_sm(a, r, lane);
-        // Vector memory operations complete in order: with the 8 just issued
-        // still out, the wave's stores before them are done.  It holds back
-        // nothing the block needs yet; it bounds what the wave has in flight.
+        // Vector memory operations complete in order: with the 8 loads of
+        // sign/mantissa bytes just issued still out, the wave's stores are done,
+        // and so are the loads of the next block's words that were issued before
+        // those 8.  The wait for the latter is part of what "hold" measured.
         if (a.hold) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
 
         wave_lds_sync();
@@ -325,7 +326,7 @@ constexpr uint32_t kWaveChoices[4] = {4, 8, 12, 16};
 // its last round and the latency of each round dominate.
 struct WaveRule {
     uint32_t per_simd;   // 0: every wave that fits
-    bool hold;           // a wave waits for its stores before its next block
+    bool hold;           // a wave waits for its stores, and its next block's words, before a block
     bool large = false;  // the largest workgroups of which two fit a CU, among equal counts
 };
 

@@ -36,7 +36,7 @@ struct DecodeArgs {
     uint32_t table_lds_bytes;
     uint32_t buf_bytes;        // exponent buffer, multiple of 16
     uint32_t twin_bufs;        // T = 1024: two block buffers alternate (else one)
-    uint32_t hold;             // T <= 128: a block starts once the last one's stores are done
+    uint32_t hold;             // T <= 128: a block's decode waits for the last one's stores
 };
 
 __device__ __forceinline__ uint32_t umin(uint32_t a, uint32_t b) { return a < b ? a : b; }

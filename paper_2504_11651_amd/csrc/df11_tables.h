@@ -24,7 +24,8 @@
 //                            minus the first length-L code (mod 2^32)
 //   then uint8 sym_sorted[256] exponents ordered by (length, value)
 //   zero padding to a multiple of 16 bytes.
-// Everything after the header is copied to LDS verbatim by the decoder.
+// The decoder stages everything after the header in LDS: the entries repacked
+// (their exponents rotated by a bit), the arrays behind them as they are.
 #pragma once
 #include <cstdint>
 
