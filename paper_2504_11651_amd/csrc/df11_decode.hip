@@ -394,8 +394,9 @@ struct WaveRule {
 
 // Chunks per CU up to which a T = 64 stream is short (4.4 rounds of five waves'
 // blocks), with 12-bit tables very short, and from which one of larger blocks
-// is long (12 rounds of two waves on 128 chunks).
-constexpr uint64_t kShortChunks = 5632, kVeryShortChunks = 3400, kLongChunks = 12288;
+// is long (12 rounds of two waves on 128 chunks) or very long (40).
+constexpr uint64_t kShortChunks = 5632, kVeryShortChunks = 3400, kLongChunks = 12288,
+                   kVeryLongChunks = 40960;
 
 WaveRule wave_rule(const df11_stream *s, uint64_t cus) {
     const df11_sizes &z = s->sizes;
@@ -419,8 +420,16 @@ WaveRule wave_rule(const df11_stream *s, uint64_t cus) {
         if (more) return {4u, true};
         if (bits < n * 2) return {0u, false};
         // two waves cover the lookups of codes of 2.4 to 2.75 bits; shorter
-        // codes make larger blocks, longer ones more lookups
-        const bool two = K > 10 && bits * 5 > n * 12 && bits * 4 < n * 11;
+        // codes make larger blocks, longer ones more lookups.  Above 2.62 bits
+        // (several standard deviations in one block) only from 40 thousand chunks
+        // per CU on: a decode that finds nothing of its stream and its output in
+        // the caches waits for them with two waves.  2 waves and 3 with hold, us,
+        // streams rotating and after 1 GiB of other reads: 218 M weights of 2.59
+        // bits 131.4, 135.2 and 136.5, 135.1; of 2.64 136.0, 136.6 and 143.6,
+        // 138.2; 260 M of 2.67 154.5, 159.6 and 160.1, 159.0.
+        const bool mixed = bits * 50 > n * 131;
+        const bool two = K > 10 && bits * 5 > n * 12 && bits * 4 < n * 11 &&
+                         (!mixed || z.num_chunks >= kVeryLongChunks * cus);
         return two ? WaveRule{2u, false} : WaveRule{3u, true};
     }
     if (T == 256) return {above(275) ? 4u : 3u, false};

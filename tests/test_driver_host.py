@@ -17,8 +17,9 @@ def llama_mats():
 
 
 def test_workspace_closed_form():
-    # up to 8 tokens the workspace holds k ranges of 1024 columns (4 for the 4096-column matrices, 14 for down); partial sums of rows x
-    # ranges x tokens floats
+    # up to 8 tokens the workspace holds k ranges of 1024 columns (4 for the
+    # 4096-column matrices, 14 for down): partial sums of rows x ranges x
+    # tokens floats
     mats, _ = llama_mats()
     few = 4 * (4096 + 1024 + 1024 + 4096 + 14336 + 14336) + 14 * 4096
     for t in (1, 7, 8):

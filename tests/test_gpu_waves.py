@@ -61,7 +61,8 @@ def one_symbol(n):
     (64, 12, gaussian, 20_000_003, 6), (64, 12, gaussian, 24_000_001, 4),
     (64, 12, gaussian, 38_000_001, 3),
     (128, 11, gaussian, 75_000_001, 4), (128, 11, gaussian, 80_000_001, 2),
-    (128, 11, two_sigmas, 80_000_001, 2), (128, 11, long_codes, 64_000_003, 3),
+    (128, 11, two_sigmas, 80_000_001, 3),
+    (128, 11, two_sigmas, 260_000_001, 2), (128, 11, long_codes, 64_000_003, 3),
     (128, 11, longer_codes, 60_000_005, 4), (128, 11, random_bits, 25_800_009, 4),
     (128, 11, short_codes, 126_000_001, 4), (128, 10, gaussian, 80_000_001, 3),
     (128, 9, gaussian, 80_000_001, 3), (128, 9, two_sigmas, 80_000_001, 4), (128, 12, gaussian, 80_000_001, 2),
