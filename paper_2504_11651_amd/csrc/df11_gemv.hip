@@ -373,7 +373,7 @@ __device__ __forceinline__ void boundary_block(const GemvArgs &g, const Tables &
 // each: in the loop, their code would cost every block scalar registers
 // (0.130 ms with it, 0.121 ms without).
 //
-// Bound: instruction issue and latency -- about 400 vector and 280 scalar
+// Bound: instruction issue and latency -- about 390 vector and 215 scalar
 // instructions per block, six waves per SIMD.  A Llama-3-8B-sized block's
 // compressed bytes alone take 57 us at the rate of a device copy; 109.5 us
 // for the two kernels.
